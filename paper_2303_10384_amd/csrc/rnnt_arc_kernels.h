@@ -404,7 +404,6 @@ __global__ __launch_bounds__(kWave * NW) void k_arc_sweep(ArcSweepParams p) {
     // the block's scores leave for global memory in one coalesced pass, from the ring
     // (a block's states all fit it); the next block's levels write the ring only after
     // the barrier that follows its stage copy
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     for (int i = tid; i < states; i += kWave * NW) {
       const int s = first.x + i;
       const double v = s_val[(s - s_begin) & (kArcRing - 1)];

@@ -121,6 +121,7 @@ __device__ __forceinline__ RowInfo lattice_row_record(const LatticeRecordSrc& s,
 
 // ---- 16-byte global accesses, optionally with the nontemporal (streaming) hint
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 template <bool NT>
 __device__ __forceinline__ uint4 load16(const uint4* p) {
@@ -246,6 +247,11 @@ struct ElemTraits<float> {
     f[2] = __uint_as_float(c.z);
     f[3] = __uint_as_float(c.w);
   }
+  template <int N>  // the elements of N 32-bit words
+  __device__ static __forceinline__ void unpack_words(const uint32_t* w, float* f) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) f[i] = __uint_as_float(w[i]);
+  }
   __device__ static __forceinline__ uint4 pack(const float* f) {
     return make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]),
                       __float_as_uint(f[3]));
@@ -282,8 +288,12 @@ struct ElemTraits<bf16_t> {
   static constexpr int kPerChunk = 8;
   __device__ static __forceinline__ void unpack(const uint4& c, float* f) {
     const uint32_t w[4] = {c.x, c.y, c.z, c.w};
+    unpack_words<4>(w, f);
+  }
+  template <int N>
+  __device__ static __forceinline__ void unpack_words(const uint32_t* w, float* f) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < N; ++i) {
       f[2 * i] = __uint_as_float(w[i] << 16);
       f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
     }
@@ -325,8 +335,12 @@ struct ElemTraits<f16_t> {
   static constexpr int kPerChunk = 8;
   __device__ static __forceinline__ void unpack(const uint4& c, float* f) {
     const uint32_t w[4] = {c.x, c.y, c.z, c.w};
+    unpack_words<4>(w, f);
+  }
+  template <int N>
+  __device__ static __forceinline__ void unpack_words(const uint32_t* w, float* f) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < N; ++i) {
       f[2 * i] = f16_to_f32(w[i] & 0xffffu);
       f[2 * i + 1] = f16_to_f32(w[i] >> 16);
     }
@@ -378,7 +392,6 @@ __device__ __forceinline__ void store_scores(__amdgpu_buffer_rsrc_t r, int lane_
   }
   if constexpr (K % 2 == 1) {
     const uint64_t a = static_cast<uint64_t>(__double_as_longlong(x[K - 1]));
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     const u32x2 v = {static_cast<uint32_t>(a), static_cast<uint32_t>(a >> 32)};
     __builtin_amdgcn_raw_buffer_store_b64(v, r, lane_off + 8 * (K - 1), row_off, 0);
   }

@@ -250,7 +250,6 @@ __global__ __launch_bounds__(64 * NW) void k2_viterbi(ViterbiParams p) {
   const __amdgpu_buffer_rsrc_t dec_rsrc = make_buffer(dec_utt, static_cast<int64_t>(ND + 1) * kCols * 8);
   // the words of diagonal 64 w + lane, all columns (0 past the stored rows)
   auto load_block = [&](int w, uint64_t (&x)[kCols]) {
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
     for (int c = 0; c < kCols; ++c) {
       const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(dec_rsrc, ((kWave * w + lane) * kCols + c) * 8, 0, 0);

@@ -4,7 +4,7 @@
 // (t, u) (Fig. 1; the wild-card arcs of Fig. 4 carry no parameter), so with
 // arc posteriors g_b, g_l and p = softmax(z):
 //   d loss / d z_v = p_v (g_b + g_l) - g_b [v = blank] - g_l [v = y_{u+1}]
-// The kernel streams the whole gradient tensor once: each 16-byte chunk is
+// The kernel streams the whole gradient tensor once: each chunk (16 bytes of gradient) is
 // located in its row(s) by index arithmetic, chunks of zero rows (padding, bad
 // utterances) are written as 0 without reading the logits, and every other
 // chunk reads the logits once and writes the gradient once.
@@ -36,12 +36,40 @@ struct GradParams {
 };
 
 constexpr int kGradChunksPerThread = 2;
-// Threads per block: 128 for float32 logits (HBM-bound: small blocks balance
-// best), 256 for 16-bit logits (eight elements per chunk, issue-bound).
-template <typename Tin>
-constexpr int kGradThreads = sizeof(Tin) == 4 ? 128 : 256;
-template <typename Tin>
-constexpr int kGradTileChunks = kGradThreads<Tin> * kGradChunksPerThread;
+// Elements per chunk: the unit a lane reads and writes at once.  16 bytes of logits when the
+// gradient has their type; for 16-bit logits and a float32 gradient the 16 bytes are the
+// gradient's, four elements from 8 bytes of logits.  Eight elements there would be two
+// 16-byte stores per lane 32 bytes apart: each store instruction of a wave then covers every
+// other half of its lines, which the nontemporal path writes as partial lines (bf16 logits
+// B=8, T=200, U=50, V=5003: K3 0.636 ms so, 0.32 ms with four elements).
+template <typename Tin, typename Tout>
+constexpr int kGradEpc = ElemTraits<Tout>::kPerChunk;
+// Threads per block: 128 for float32 gradients (HBM-bound: small blocks balance
+// best), 256 for 16-bit ones (eight elements per chunk, issue-bound).
+template <typename Tout>
+constexpr int kGradThreads = sizeof(Tout) == 4 ? 128 : 256;
+template <typename Tout>
+constexpr int kGradTileChunks = kGradThreads<Tout> * kGradChunksPerThread;
+
+// The logits of one chunk as 32-bit words.
+template <typename Tin, int EPC>
+struct LogitChunk {
+  static constexpr int kBytes = EPC * static_cast<int>(sizeof(Tin));
+  static_assert(kBytes == 16 || kBytes == 8, "a chunk of logits is 16 or 8 bytes");
+  uint32_t w[kBytes / 4];
+
+  template <bool NT>
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, int off) {
+    if constexpr (kBytes == 16) {
+      const u32x4 v = buffer_load16<NT>(r, off);
+      w[0] = v.x, w[1] = v.y, w[2] = v.z, w[3] = v.w;
+    } else {
+      const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, NT ? kBufferNT : 0);
+      w[0] = v.x, w[1] = v.y;
+    }
+  }
+  __device__ __forceinline__ void unpack(float (&f)[EPC]) const { ElemTraits<Tin>::template unpack_words<kBytes / 4>(w, f); }
+};
 
 __device__ __forceinline__ float grad_elem(float z, int v, const RowInfo& ri, int blank) {
   const float pr = fast_exp2(fmaf(z, kLog2eF, -ri.lse2));
@@ -51,15 +79,11 @@ __device__ __forceinline__ float grad_elem(float z, int v, const RowInfo& ri, in
   return (ri.label == kZeroRow) ? 0.f : g;
 }
 
-// Gradient elements of one 16-byte input chunk, stored as Tout (one or two
-// aligned 16-byte stores).
+// The gradient elements of one chunk: one aligned 16-byte store.
 template <typename Tout, int EPC>
 __device__ __forceinline__ void store_chunk(void* dst, int64_t e0, const float* out) {
-  constexpr int PER = ElemTraits<Tout>::kPerChunk;
-  static_assert(EPC % PER == 0, "input chunk must cover whole output chunks");
-  uint4* d = reinterpret_cast<uint4*>(static_cast<Tout*>(dst) + e0);
-#pragma unroll
-  for (int i = 0; i < EPC / PER; ++i) store16<kK3StreamStores>(d + i, ElemTraits<Tout>::pack(out + i * PER));
+  static_assert(EPC == ElemTraits<Tout>::kPerChunk, "a chunk is 16 bytes of the gradient");
+  store16<kK3StreamStores>(reinterpret_cast<uint4*>(static_cast<Tout*>(dst) + e0), ElemTraits<Tout>::pack(out));
 }
 
 // The chunks of one block, one at a time (any V; the tensor's final partial
@@ -70,10 +94,13 @@ __device__ __forceinline__ void store_chunk(void* dst, int64_t e0, const float* 
 template <typename T, typename Tout, bool SMALLV>
 __device__ __forceinline__ void grad_chunks_general(const GradParams& p, int64_t tile0, int64_t r_tile,
                                                     uint32_t v_tile) {
-  constexpr int EPC = ElemTraits<T>::kPerChunk;
-  constexpr int kThreads = kGradThreads<T>;
+  constexpr int EPC = kGradEpc<T, Tout>;
+  constexpr int kThreads = kGradThreads<Tout>;
   const uint32_t uV = static_cast<uint32_t>(p.V);
-  const uint4* __restrict__ src = static_cast<const uint4*>(p.logits);
+  const int64_t left = p.n_elem - tile0 * EPC;  // elements from the tile's first on
+  const __amdgpu_buffer_rsrc_t rsrc = make_buffer(
+      static_cast<const T*>(p.logits) + tile0 * EPC,
+      min<int64_t>(left, kGradTileChunks<Tout> * EPC) * static_cast<int64_t>(sizeof(T)));
   const T* __restrict__ src_e = static_cast<const T*>(p.logits);
   Tout* __restrict__ dst_e = static_cast<Tout*>(p.grad);
   for (int q = 0; q < kGradChunksPerThread; ++q) {
@@ -89,7 +116,9 @@ __device__ __forceinline__ void grad_chunks_general(const GradParams& p, int64_t
     float f[EPC], out[EPC];
     RowInfo ri = p.rowinfo[r];
     if (full) {
-      ElemTraits<T>::unpack(load16<kK3StreamLoads>(src + c), f);
+      LogitChunk<T, EPC> z;
+      z.template load<kK3StreamLoads>(rsrc, cl * z.kBytes);
+      z.unpack(f);
     } else {
 #pragma unroll
       for (int j = 0; j < EPC; ++j) f[j] = (e0 + j < p.n_elem) ? ElemTraits<T>::load1(src_e + e0 + j) : 0.f;
@@ -115,7 +144,7 @@ __device__ __forceinline__ void grad_chunks_general(const GradParams& p, int64_t
 }
 
 // Tin: logits element type; Tout: gradient element type (Tin or float).
-// A block covers kGradTileChunks<Tin> consecutive chunks.  Every block but the one
+// A block covers kGradTileChunks<Tout> consecutive chunks.  Every block but the one
 // holding the tensor's final partial chunk takes the fast path, in three phases
 // that keep all of a thread's memory requests in flight together: the row
 // records of its chunks; the logits of its chunks, as buffer loads issued
@@ -123,11 +152,12 @@ __device__ __forceinline__ void grad_chunks_general(const GradParams& p, int64_t
 // buffer's end, which reads zero without touching memory); arithmetic and
 // stores.
 template <typename Tin, typename Tout, bool SMALLV>
-__global__ __launch_bounds__(kGradThreads<Tin>) void k3_grad(GradParams p) {
+__global__ __launch_bounds__(kGradThreads<Tout>) void k3_grad(GradParams p) {
   using T = Tin;
-  constexpr int EPC = ElemTraits<T>::kPerChunk;
-  constexpr int kThreads = kGradThreads<Tin>;
-  constexpr int kTile = kGradTileChunks<Tin>;
+  constexpr int EPC = kGradEpc<Tin, Tout>;
+  constexpr int kThreads = kGradThreads<Tout>;
+  constexpr int kTile = kGradTileChunks<Tout>;
+  constexpr int kBytes = LogitChunk<Tin, EPC>::kBytes;
   constexpr int Q = kGradChunksPerThread;
   const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * kTile;
   const int64_t e_tile = tile0 * EPC;
@@ -153,9 +183,9 @@ __global__ __launch_bounds__(kGradThreads<Tin>) void k3_grad(GradParams p) {
     ri1[q] = p.rowinfo[min(r[q] + 1, p.n_rows - 1)];
   }
   __builtin_amdgcn_sched_barrier(0);  // all record loads issue before any of them is used
-  const int64_t tile_bytes = min<int64_t>(kTile, n_full - tile0) * 16;
-  const __amdgpu_buffer_rsrc_t rsrc = make_buffer(static_cast<const uint4*>(p.logits) + tile0, tile_bytes);
-  u32x4 raw[Q];
+  const int64_t tile_bytes = min<int64_t>(kTile, n_full - tile0) * kBytes;
+  const __amdgpu_buffer_rsrc_t rsrc = make_buffer(static_cast<const T*>(p.logits) + e_tile, tile_bytes);
+  LogitChunk<T, EPC> raw[Q];
   bool store[Q];
   bool any_row[Q];  // some lane's chunk q touches a row with a gradient
 #pragma unroll
@@ -166,14 +196,13 @@ __global__ __launch_bounds__(kGradThreads<Tin>) void k3_grad(GradParams p) {
     const bool zero = ri0[q].label == kZeroRow && (!split || ri1[q].label == kZeroRow);
     store[q] = live;
     any_row[q] = __builtin_amdgcn_ballot_w64(live && !zero) != 0;
-    const int off = (live && !zero) ? cl * 16 : kOutOfRange;
-    raw[q] = buffer_load16<kK3StreamLoads>(rsrc, off);
+    raw[q].template load<kK3StreamLoads>(rsrc, (live && !zero) ? cl * kBytes : kOutOfRange);
   }
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     float f[EPC], out[EPC];
-    ElemTraits<T>::unpack(make_uint4(raw[q].x, raw[q].y, raw[q].z, raw[q].w), f);
+    raw[q].unpack(f);
     if (any_row[q] && __builtin_amdgcn_ballot_w64(v[q] + EPC > p.V) == 0) {
       // no chunk q of the wave reaches past its row's end: one record per lane
 #pragma unroll
@@ -209,8 +238,8 @@ __global__ __launch_bounds__(kGradThreads<Tin>) void k3_grad(GradParams p) {
 // hold (padding logits may be NaN).  The at most four corrections -g_b at
 // v = blank and -g_l at v = y_{u+1} are applied by the lane owning the element,
 // at a position known to the whole wave.
-template <typename Tin>
-constexpr int kWideMinV = kWave * ElemTraits<Tin>::kPerChunk - 1;
+template <typename Tin, typename Tout>
+constexpr int kWideMinV = kWave * kGradEpc<Tin, Tout> - 1;
 
 // out[j] -= corr in lane `owner` for the wave-uniform slot js (no run-time index
 // into out: the slot is matched against each constant j)
@@ -250,11 +279,12 @@ __device__ __forceinline__ bool one_exp_shift(const RowInfo& r, float& s, float&
 }
 
 template <typename Tin, typename Tout>
-__global__ __launch_bounds__(kGradThreads<Tin>) void k3_grad_wide(GradParams p) {
+__global__ __launch_bounds__(kGradThreads<Tout>) void k3_grad_wide(GradParams p) {
   using T = Tin;
-  constexpr int EPC = ElemTraits<T>::kPerChunk;
-  constexpr int kThreads = kGradThreads<Tin>;
-  constexpr int kTile = kGradTileChunks<Tin>;
+  constexpr int EPC = kGradEpc<Tin, Tout>;
+  constexpr int kThreads = kGradThreads<Tout>;
+  constexpr int kTile = kGradTileChunks<Tout>;
+  constexpr int kBytes = LogitChunk<Tin, EPC>::kBytes;
   constexpr int Q = kGradChunksPerThread;
   const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * kTile;
   const int64_t e_tile = tile0 * EPC;
@@ -283,9 +313,9 @@ __global__ __launch_bounds__(kGradThreads<Tin>) void k3_grad_wide(GradParams p) 
     Rb[q] = rows[min(ra + 1, p.n_rows - 1)];
   }
   __builtin_amdgcn_sched_barrier(0);  // all record loads issue before any of them is used
-  const int64_t tile_bytes = min<int64_t>(kTile, n_full - tile0) * 16;
-  const __amdgpu_buffer_rsrc_t rsrc = make_buffer(static_cast<const uint4*>(p.logits) + tile0, tile_bytes);
-  u32x4 raw[Q];
+  const int64_t tile_bytes = min<int64_t>(kTile, n_full - tile0) * kBytes;
+  const __amdgpu_buffer_rsrc_t rsrc = make_buffer(static_cast<const T*>(p.logits) + e_tile, tile_bytes);
+  LogitChunk<T, EPC> raw[Q];
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const int cl = q * kThreads + static_cast<int>(threadIdx.x);
@@ -293,7 +323,7 @@ __global__ __launch_bounds__(kGradThreads<Tin>) void k3_grad_wide(GradParams p) 
     const int v = va[q] + lane * EPC;  // column of the chunk's first element in row a (>= V: in row b)
     const bool za = Ra[q].label == kZeroRow, zb = Rb[q].label == kZeroRow;
     const bool zero = v >= p.V ? zb : (v + EPC > p.V ? za && zb : za);
-    raw[q] = buffer_load16<kK3StreamLoads>(rsrc, (live && !zero) ? cl * 16 : kOutOfRange);
+    raw[q].template load<kK3StreamLoads>(rsrc, (live && !zero) ? cl * kBytes : kOutOfRange);
   }
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -307,7 +337,7 @@ __global__ __launch_bounds__(kGradThreads<Tin>) void k3_grad_wide(GradParams p) 
       for (int j = 0; j < EPC; ++j) out[j] = 0.f;
     } else {
       float f[EPC];
-      ElemTraits<T>::unpack(make_uint4(raw[q].x, raw[q].y, raw[q].z, raw[q].w), f);
+      raw[q].unpack(f);
       // p_v (g_b + g_l) = 2^(z_v log2 e - s) * m per row: s = lse2 - log2(g_b + g_l) and m = 1
       // while |lse2| < kOneExpMaxLse2, else s = lse2 and m = g_b + g_l (see one_exp_shift)
       float sa, ma, sb, mb;
