@@ -377,6 +377,7 @@ rnnt_status_t rnnt_loss_timed(const void* logits, rnnt_shape_t shape, const int3
     p3.n_elem = n_elem;
     p3.n_rows = n_rows;
     p3.V = shape.V;
+    p3.inv_V = 1.0 / shape.V;
     p3.blank = blank;
     if (launch_grad(shape.dtype, shape.grad_dtype, p3, stream) != hipSuccess) return RNNT_ERR_HIP;
   }
@@ -608,6 +609,7 @@ rnnt_status_t rnnt_arc_loss_timed(const void* logits, rnnt_shape_t shape, const 
     p3.n_elem = n_rows * shape.V;
     p3.n_rows = n_rows;
     p3.V = shape.V;
+    p3.inv_V = 1.0 / shape.V;
     p3.blank = plan->blank;
     if (launch_grad(shape.dtype, shape.grad_dtype, p3, stream) != hipSuccess) return RNNT_ERR_HIP;
     ArcExtraParams px{};
