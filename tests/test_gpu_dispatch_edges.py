@@ -34,3 +34,20 @@ def check(torch, pkg, B, T, U, V, seed, variant="rnnt", dtype="f32", grad_dtype=
 @pytest.mark.parametrize("V", [2, 3, 4, 5, 9, 254, 255, 257, 511, 1023])
 def test_float32_gradient_of_half_logits(torch, pkg, dtype, V):  # noqa: F811
     check(torch, pkg, 3, 5, 6, V, seed=100 + V, dtype=dtype, grad_dtype="f32", blank=V - 1)
+
+
+# blocks of the populate kernel: float32 rows of up to 128 KB a block (V = 128: 256 rows; 513: 63;
+# 1023: 32), units at and past a block's end, and the row groups of equal coverage (V / 4 or V / 8
+# interior chunks of 8, 16, 32, 64: two chunks for half the lanes)
+@pytest.mark.parametrize("V,U,dtype", [(33, 255, "f32"), (33, 256, "f32"), (65, 300, "f32"), (128, 70, "f32"),
+                                       (257, 126, "f32"), (257, 128, "f32"), (513, 62, "f32"), (513, 63, "f32"),
+                                       (1023, 33, "f32"), (64, 40, "bf16"), (129, 40, "f16"), (257, 20, "bf16"),
+                                       (513, 20, "f16")])
+def test_populate_blocks_and_groups(torch, pkg, V, U, dtype):  # noqa: F811
+    check(torch, pkg, 2, 5, U, V, seed=V + U, dtype=dtype, full=U % 2 == 0)
+
+
+# few frames: blocks cut to a few rounds of their row groups (units just past a cut)
+@pytest.mark.parametrize("V,U,dtype", [(1025, 16, "f32"), (1025, 33, "bf16"), (257, 65, "f16"), (513, 150, "bf16")])
+def test_populate_blocks_of_few_frames(torch, pkg, V, U, dtype):  # noqa: F811
+    check(torch, pkg, 1, 4, U, V, seed=V + U, dtype=dtype, full=True)
