@@ -99,6 +99,20 @@ ViterbiLayout make_viterbi_layout(const rnnt_shape_t& s) {
   return L;
 }
 
+size_t elem_bytes(int dt) { return dt == RNNT_DTYPE_F32 ? 4 : 2; }
+
+// Whether kernel 1 loads the logits through the caches for kernel 3 to find: while logits
+// and gradient together stay within kKeepBytes, nine times the memory-side cache.  Measured
+// (V = 1025 and 5003, per call, nontemporal and ordinary loads): 0.54 GB 118 and 102 us,
+// 1.1 GB 206 and 179, 2.15 GB 380 and 360, 2.4 GB (16-bit) 414 and 405; past it the
+// gradient's own lines push the logits out, and ordinary loads only slow kernel 1 (2.45 GB
+// with a float32 gradient of 16-bit logits 458 and 466 us, 5.3 GB 818 and 835).
+constexpr size_t kKeepBytes = static_cast<size_t>(9) << 28;
+bool keep_logits(const rnnt_shape_t& s, bool need_grad) {
+  const size_t n = static_cast<size_t>(s.B) * s.T_max * (static_cast<size_t>(s.U_max) + 1) * s.V;
+  return need_grad && n * (elem_bytes(s.dtype) + elem_bytes(s.grad_dtype)) <= kKeepBytes;
+}
+
 bool aligned16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15u) == 0; }
 
 // Stream-ordered workspace when the caller passes none.
@@ -320,6 +334,7 @@ rnnt_status_t rnnt_loss_timed(const void* logits, rnnt_shape_t shape, const int3
   p1.label_lens = label_lens;
   p1.n_elem = n_elem;
   p1.lp2 = reinterpret_cast<double2*>(ws + L.lp2);
+  p1.keep_logits = keep_logits(shape, need_grad);
   p1.pack_lse2f = 1;  // the posterior kernel reads lse2f from the weights
   if (launch_populate_lattice(shape.dtype, p1, stream) != hipSuccess) return RNNT_ERR_HIP;
   if (mark(1) != hipSuccess) return RNNT_ERR_HIP;
@@ -525,6 +540,7 @@ rnnt_status_t rnnt_arc_loss_timed(const void* logits, rnnt_shape_t shape, const 
   p1.n_elem = n_rows * shape.V;
   p1.lse2_rows = reinterpret_cast<double*>(ws + L.lse2);
   p1.clear_flags = reinterpret_cast<int32_t*>(ws + L.bad);
+  p1.keep_logits = keep_logits(shape, grad_out != nullptr);
   if (launch_populate_rows(shape.dtype, p1, stream) != hipSuccess) return RNNT_ERR_HIP;
   if (mark(1) != hipSuccess) return RNNT_ERR_HIP;
 

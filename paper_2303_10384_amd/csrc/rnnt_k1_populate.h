@@ -43,21 +43,15 @@
 // offsets past the buffer's end (zeros, no memory access), so every load is
 // issued unconditionally and the compiler's wait counts stay exact.  Results
 // go to LDS and leave the block in one contiguous copy at its end, so no
-// global store sits in the row loop either.  Otherwise (rows longer than
-// 64 * 5 interior chunks, a block reaching the tensor's final partial chunk,
-// or a block spanning 2 GB or more) a general loop with a running (max, sum)
-// per lane and element masks.
+// global store sits in the row loop either.  Rows longer than 64 * 5 interior chunks go
+// through the same two register sets in pieces (LONG).  Otherwise (a block reaching the
+// tensor's final partial chunk, or spanning 2 GB or more) a general loop with a running
+// (max, sum) per lane and element masks.
 #pragma once
 
 #include "rnnt_device.h"
 
-#ifndef RNNT_K1_NT_LOAD
-#define RNNT_K1_NT_LOAD 1
-#endif
-
 namespace rnnt {
-
-constexpr bool kK1StreamLoads = RNNT_K1_NT_LOAD != 0;
 
 constexpr int kK1Dense = 0;
 constexpr int kK1Lattice = 1;
@@ -83,6 +77,7 @@ struct PopulateParams {
   // rows form
   double* lse2_rows;       // (B, T_max, U_max+1): lse2f, as lse2
   int32_t* clear_flags;    // (B) set to 0 by block 0 (the arc-list loss's bad-data flags), or null
+  int32_t keep_logits;     // nonzero: ordinary loads, the logits are read again while the caches hold some
 };
 
 // (max, sum of exp) of one batch of register-held values, merged into the
@@ -160,7 +155,7 @@ __device__ __forceinline__ float issue_label_elem(__amdgpu_buffer_rsrc_t rsrc, c
 // leaves z[y] for a later issue_label_elem.  Offsets are unsigned: a row that
 // is not live starts at kOutOfRange, and every offset derived from it stays at
 // or above 2^31, past the buffer.
-template <typename T, int G, int NB, bool WITH_LABEL = true>
+template <typename T, int G, int NB, bool NT, bool WITH_LABEL = true>
 __device__ __forceinline__ void issue_row(__amdgpu_buffer_rsrc_t rsrc, const RowGeom& g, int V, int blank, int lg,
                                           RowRegs<T, G, NB>& R) {
   constexpr int EPC = ElemTraits<T>::kPerChunk;
@@ -175,7 +170,7 @@ __device__ __forceinline__ void issue_row(__amdgpu_buffer_rsrc_t rsrc, const Row
 #pragma unroll
   for (int q = 0; q < NB; ++q) {
     const int k = min(max(kf + q * G + lg, kint_lo), kint_hi);
-    R.raw[q] = buffer_load16<kK1StreamLoads>(rsrc, static_cast<int>(rb + static_cast<uint32_t>(k) * 16u));
+    R.raw[q] = buffer_load16<NT>(rsrc, static_cast<int>(rb + static_cast<uint32_t>(k) * 16u));
   }
   // the partial boundary chunks, one element per lane (their lines come in with the interior loads)
 #pragma unroll
@@ -266,6 +261,72 @@ __device__ __forceinline__ void reduce_row(const RowRegs<T, G, NB>& R, const Row
   sg = static_cast<double>(sgf);
 }
 
+// Long rows (more interior chunks than the registers of one row hold): a row goes
+// through in pieces of 64 * NB interior chunks, its boundary elements, z[blank] and
+// z[y] with the first.  Issue the loads of piece `pc` of a row.
+template <typename T, int NB, bool NT>
+__device__ __forceinline__ void issue_piece(__amdgpu_buffer_rsrc_t rsrc, const RowGeom& g, int pc, int V, int blank,
+                                            int lane, RowRegs<T, kWave, NB>& R) {
+  constexpr int EPC = ElemTraits<T>::kPerChunk;
+  const int kf = g.mis != 0 ? 1 : 0;
+  const int kl = g.nch - 1 - (((g.mis + V) % EPC) != 0 ? 1 : 0);
+  const uint32_t rb = g.live ? static_cast<uint32_t>(g.off0) : static_cast<uint32_t>(kOutOfRange);
+  const int k0 = kf + pc * (kWave * NB) + lane;
+#pragma unroll
+  for (int q = 0; q < NB; ++q) {  // past the row's last interior chunk: no memory access
+    const int k = k0 + q * kWave;
+    R.raw[q] = buffer_load16<NT>(
+        rsrc, static_cast<int>(k <= kl ? rb + static_cast<uint32_t>(k) * 16u : static_cast<uint32_t>(kOutOfRange)));
+  }
+  const bool head = pc == 0;
+  const BndSlot b = bnd_slot<EPC>(g, V, lane);
+  R.xb[0] = buffer_load_elem<T>(
+      rsrc, static_cast<int>(head && b.ok ? rb + static_cast<uint32_t>(b.col + g.mis) * static_cast<uint32_t>(sizeof(T))
+                                          : static_cast<uint32_t>(kOutOfRange)));
+  R.zb = buffer_load_elem<T>(
+      rsrc, static_cast<int>(head ? rb + static_cast<uint32_t>(g.mis + blank) * static_cast<uint32_t>(sizeof(T))
+                                  : static_cast<uint32_t>(kOutOfRange)));
+  RowGeom gy = g;
+  gy.live = g.live && head;
+  R.zy = issue_label_elem<T>(rsrc, gy, V);
+}
+
+// Lane sum of 2^(z log2 e - sh2) over the lane's elements of one piece.  With
+// `take_max` (the wave's first piece) the shift is set from the piece's maximum first.
+template <typename T, int NB>
+__device__ __forceinline__ float piece_sum(const RowRegs<T, kWave, NB>& R, const RowGeom& g, int pc, int V, int lane,
+                                           bool take_max, float& sh2) {
+  constexpr int EPC = ElemTraits<T>::kPerChunk;
+  const float kNegInf = -__builtin_inff();
+  const int kf = g.mis != 0 ? 1 : 0;
+  const int kl = g.nch - 1 - (((g.mis + V) % EPC) != 0 ? 1 : 0);
+  const int k0 = kf + pc * (kWave * NB) + lane;
+  const float xb = (pc == 0 && bnd_slot<EPC>(g, V, lane).ok) ? R.xb[0] : kNegInf;
+  float x[NB * EPC];
+#pragma unroll
+  for (int q = 0; q < NB; ++q) ElemTraits<T>::unpack(make_uint4(R.raw[q].x, R.raw[q].y, R.raw[q].z, R.raw[q].w),
+                                                     x + q * EPC);
+  if (take_max) {
+    float m = xb;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+#pragma unroll
+      for (int j = 0; j < EPC; ++j) m = (k0 + q * kWave <= kl) ? fmaxf(m, x[q * EPC + j]) : m;
+    }
+    const float mg = group_reduce<kWave, MaxOp>(m, kNegInf);
+    sh2 = (mg == kNegInf) ? 0.f : mg * kLog2eF;
+  }
+  float s = fast_exp2(fmaf(xb, kLog2eF, -sh2));
+#pragma unroll
+  for (int q = 0; q < NB; ++q) {
+    float sq = fast_exp2(fmaf(x[q * EPC], kLog2eF, -sh2));
+#pragma unroll
+    for (int j = 1; j < EPC; ++j) sq += fast_exp2(fmaf(x[q * EPC + j], kLog2eF, -sh2));
+    s += (k0 + q * kWave <= kl) ? sq : 0.f;
+  }
+  return s;
+}
+
 // Row statistics for any row: batches of NB chunks per lane with a running
 // (max, sum) per lane, element masks everywhere, element loads where the row
 // reaches into the tensor's final partial chunk.
@@ -323,8 +384,15 @@ constexpr int kXcds = 8;
 constexpr int kXcdRun = RNNT_K1_XCD_RUN;  // consecutive blocks per XCD turn
 
 
-template <typename T, int G, int NB, int OUT, bool FAST>
+//
+// LONG: rows longer than a wave's registers, taken in pieces (issue_piece): float32 rows of
+// 5003, B=8 T=200 U=60, 210 us by the batched path, 186 us by pieces; bf16 ones 115 and 101 us.
+// NT: the logits are loaded with the nontemporal hint.  It keeps a stream that nothing reads
+// again before it is gone from the caches out of them; without it the gradient kernel finds
+// part of the logits in the 256 MB memory-side cache (the launcher picks, see keep_logits).
+template <typename T, int G, int NB, int OUT, bool FAST, bool NT = true, bool LONG = false>
 __global__ __launch_bounds__(256) void k1_populate(PopulateParams p) {
+  static_assert(!LONG || G == kWave, "long rows take a whole wave");
   constexpr int EPC = ElemTraits<T>::kPerChunk;
   constexpr int GROUPS = 256 / G;  // rows in flight per block
   // per row: the label, then the group results (shift, sum of exponentials, z[blank], z[y])
@@ -408,24 +476,90 @@ __global__ __launch_bounds__(256) void k1_populate(PopulateParams p) {
         s_zy[g.j] = R.zy;
       }
     };
+    if constexpr (LONG) {
+      // the pieces of the wave's rows as one sequence, two register sets in turn: a
+      // piece's loads go out before the piece before it is summed, across row ends too
+      const int n_pc = (p.V / EPC + kWave * NB - 1) / (kWave * NB);
+      stage_labels();
+      float acc = 0.f, zb = 0.f, zy = 0.f;
+      bool first = true;
+      auto take = [&](const RowRegs<T, G, NB>& R, const RowGeom& g, int pc) {
+        const float s = piece_sum<T, NB>(R, g, pc, p.V, lg, first, sh2);
+        first = false;
+        if (pc == 0) {
+          acc = s;
+          zb = R.zb;
+          zy = R.zy;
+        } else {
+          acc += s;
+        }
+        if (pc < n_pc - 1 || !g.live) return;  // wave-uniform
+        float sgf = group_reduce<G, SumOp>(acc, 0.f);
+        double sg;
+        double shift = sh2;
+        if (sgf >= kSumLo && sgf <= kSumHi) {
+          sg = static_cast<double>(sgf);
+        } else {  // the row's range lies far from the shift (or it holds a NaN): running maxima, and a new shift
+          float mg;
+          const int64_t e0 = e_first + static_cast<int64_t>(g.j) * p.V;
+          row_stats_general<T, G, NB>(base, e0, e0 / EPC, g.mis, g.nch, p.V, full_chunks, lg, mg, sg);
+          shift = static_cast<double>(mg) * static_cast<double>(kLog2eF);  // what that sum is relative to
+          if (__builtin_isfinite(mg)) sh2 = static_cast<float>(shift);
+        }
+        if (lg == 0) {
+          s_shift2[g.j] = shift;
+          s_sum[g.j] = sg;
+          s_zb[g.j] = zb;
+          s_zy[g.j] = zy;
+        }
+      };
+      RowRegs<T, G, NB> R0, R1;
+      RowGeom g0 = geom(0, true), g1;
+      int it = 0, pc = 0;  // the next piece to issue
+      auto advance = [&]() {
+        if (++pc == n_pc) {
+          pc = 0;
+          ++it;
+        }
+      };
+      issue_piece<T, NB, NT>(rsrc, g0, 0, p.V, p.blank, lg, R0);
+      int pc0 = 0, pc1 = 0;
+      advance();
+      const int n_steps = n_iter * n_pc;
+      for (int q = 0; q < n_steps; q += 2) {
+        g1 = geom(it, true);
+        pc1 = pc;
+        issue_piece<T, NB, NT>(rsrc, g1, pc1, p.V, p.blank, lg, R1);
+        advance();
+        __builtin_amdgcn_sched_barrier(0);  // the next piece's loads go out before this one is summed
+        take(R0, g0, pc0);
+        g0 = geom(it, true);
+        pc0 = pc;
+        issue_piece<T, NB, NT>(rsrc, g0, pc0, p.V, p.blank, lg, R0);
+        advance();
+        __builtin_amdgcn_sched_barrier(0);
+        take(R1, g1, pc1);
+      }
+    } else {
     // two register sets in turn (a copy between them would wait for the loads in flight);
     // the first row's chunks go out before the labels are staged, its z[y] after
     RowGeom g0 = geom(0, false), g1;
     RowRegs<T, G, NB> R0, R1;
-    issue_row<T, G, NB, false>(rsrc, g0, p.V, p.blank, lg, R0);
+    issue_row<T, G, NB, NT, false>(rsrc, g0, p.V, p.blank, lg, R0);
     __builtin_amdgcn_sched_barrier(0);
     stage_labels();
     g0.y = group_uniform(s_label[g0.j]);
     R0.zy = issue_label_elem<T>(rsrc, g0, p.V);
     for (int it = 0; it < n_iter; it += 2) {
       g1 = geom(it + 1, true);  // past the block's rows: not live, no memory access
-      issue_row<T, G, NB>(rsrc, g1, p.V, p.blank, lg, R1);
+      issue_row<T, G, NB, NT>(rsrc, g1, p.V, p.blank, lg, R1);
       __builtin_amdgcn_sched_barrier(0);  // the next row's loads go out before this row is reduced
       finish(R0, g0, it == 0);
       g0 = geom(it + 2, true);
-      issue_row<T, G, NB>(rsrc, g0, p.V, p.blank, lg, R0);
+      issue_row<T, G, NB, NT>(rsrc, g0, p.V, p.blank, lg, R0);
       __builtin_amdgcn_sched_barrier(0);
       finish(R1, g1, false);
+    }
     }
   } else {
     stage_labels();

@@ -18,7 +18,7 @@ namespace {  // each including unit keeps its own copy
 
 // Lanes per row G and interior chunks per lane NB: the smallest G*NB that
 // covers a row's interior chunks (at most V / EPC of them) with NB <= 5; rows
-// with more take the batched path (G = 64, NB = 5).
+// with more go in pieces of 64 * kPieceChunks (2, 3 and 8 chunks a lane were slower).
 struct K1Shape {
   int G, NB;
   bool fast;
@@ -75,26 +75,37 @@ void k1_blocking(PopulateParams& p, int elem_bytes, int G) {
   p.rows_per_block = (U1 + p.n_ublk - 1) / p.n_ublk;
 }
 
-template <typename T, int G, int NB, int OUT, bool FAST>
+constexpr int kPieceChunks = 4;
+
+template <typename T, int G, int NB, int OUT, bool FAST, bool NT = true, bool LONG = false>
 hipError_t launch_k1_g(PopulateParams p, hipStream_t stream) {
   k1_blocking(p, static_cast<int>(sizeof(T)), G);
   const int64_t blocks = static_cast<int64_t>(p.B) * p.T_max * p.n_ublk;
   const int64_t runs = (blocks + kXcdRun - 1) / kXcdRun;  // whole rounds of the XCD-major numbering
   const int64_t grid = (runs + kXcds - 1) / kXcds * kXcds * kXcdRun;
   if (grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((k1_populate<T, G, NB, OUT, FAST>), dim3(static_cast<uint32_t>(grid)), dim3(256), 0,
+  hipLaunchKernelGGL((k1_populate<T, G, NB, OUT, FAST, NT, LONG>), dim3(static_cast<uint32_t>(grid)), dim3(256), 0,
                      stream, p);
   return hipGetLastError();
+}
+
+// the two load forms; the populate step on its own has no gradient after it
+template <typename T, int G, int NB, int OUT, bool LONG>
+hipError_t launch_k1_nt(const PopulateParams& p, hipStream_t stream) {
+  if constexpr (OUT != kK1Dense) {
+    if (p.keep_logits) return launch_k1_g<T, G, NB, OUT, true, false, LONG>(p, stream);
+  }
+  return launch_k1_g<T, G, NB, OUT, true, true, LONG>(p, stream);
 }
 
 template <typename T, int G, int OUT>
 hipError_t launch_k1_nb(int nb, const PopulateParams& p, hipStream_t stream) {
   switch (nb) {
-    case 1: return launch_k1_g<T, G, 1, OUT, true>(p, stream);
-    case 2: return launch_k1_g<T, G, 2, OUT, true>(p, stream);
-    case 3: return launch_k1_g<T, G, 3, OUT, true>(p, stream);
-    case 4: return launch_k1_g<T, G, 4, OUT, true>(p, stream);
-    default: return launch_k1_g<T, G, 5, OUT, true>(p, stream);
+    case 1: return launch_k1_nt<T, G, 1, OUT, false>(p, stream);
+    case 2: return launch_k1_nt<T, G, 2, OUT, false>(p, stream);
+    case 3: return launch_k1_nt<T, G, 3, OUT, false>(p, stream);
+    case 4: return launch_k1_nt<T, G, 4, OUT, false>(p, stream);
+    default: return launch_k1_nt<T, G, 5, OUT, false>(p, stream);
   }
 }
 
@@ -108,7 +119,8 @@ bool k1_span_fits(PopulateParams p, int elem_bytes) {
 template <typename T, int OUT>
 hipError_t launch_k1(const PopulateParams& p, hipStream_t stream) {
   const K1Shape ks = k1_shape<T>(p.V);
-  if (!ks.fast || !k1_span_fits(p, static_cast<int>(sizeof(T)))) return launch_k1_g<T, 64, 5, OUT, false>(p, stream);
+  if (!k1_span_fits(p, static_cast<int>(sizeof(T)))) return launch_k1_g<T, 64, 5, OUT, false>(p, stream);
+  if (!ks.fast) return launch_k1_nt<T, 64, kPieceChunks, OUT, true>(p, stream);
   switch (ks.G) {
     case 8: return launch_k1_nb<T, 8, OUT>(ks.NB, p, stream);
     case 16: return launch_k1_nb<T, 16, OUT>(ks.NB, p, stream);

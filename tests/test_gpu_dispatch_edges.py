@@ -4,6 +4,7 @@ absolute; 16-bit logits: loss 2e-3 relative, gradient 2e-3 relative + 1e-5, plus
 rounding where the gradient is stored in bf16)."""
 import sys
 
+import numpy as np
 import pytest
 
 from oracle import rnnt_ref as R
@@ -51,3 +52,26 @@ def test_populate_blocks_and_groups(torch, pkg, V, U, dtype):  # noqa: F811
 @pytest.mark.parametrize("V,U,dtype", [(1025, 16, "f32"), (1025, 33, "bf16"), (257, 65, "f16"), (513, 150, "bf16")])
 def test_populate_blocks_of_few_frames(torch, pkg, V, U, dtype):  # noqa: F811
     check(torch, pkg, 1, 4, U, V, seed=V + U, dtype=dtype, full=True)
+
+
+# rows taken in pieces (more than 320 interior chunks: V of about 1284 float32 and 2567 16-bit
+# elements; pieces of 1024 and 2048): the edges of the rule and of the pieces, a block with fewer
+# rows than waves, rows whose range moves far from the one before (a new shift), and a NaN row
+@pytest.mark.parametrize("V,dtype", [(1283, "f32"), (1284, "f32"), (1287, "f32"), (2048, "f32"), (2051, "f32"),
+                                     (3077, "f32"), (2567, "bf16"), (2568, "bf16"), (4096, "f16"), (6155, "bf16")])
+def test_populate_rows_in_pieces(torch, pkg, V, dtype):  # noqa: F811
+    check(torch, pkg, 2, 3, 5, V, seed=V, dtype=dtype, blank=V - 1)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_pieces_of_rows_far_apart(torch, pkg, dtype):  # noqa: F811
+    V = 3000
+    logits, tl, ul, labels = W.small_case(2, 4, 6, V, 5, sigma=1.5, full=True)
+    # up to 60 nats between neighbouring rows, and the largest element of some rows in the last piece
+    logits += np.random.default_rng(6).uniform(-30.0, 30.0, size=logits.shape[:3] + (1,)).astype(np.float32)
+    logits[:, 1:3, ::2, V - 3] += 40.0
+    logits[0, 2, 3, 17] = np.nan
+    loss, grad, seen = run_case(torch, pkg, logits, tl, ul, labels, dtype=dtype)
+    assert np.isnan(loss[0]) and not np.isnan(loss[1])
+    loss_ref, grad_ref = R.rnnt_loss_grad(seen[1:], labels[1:], tl[1:], ul[1:], 0, "rnnt")
+    tol_check(loss[1:], grad[1:], loss_ref, grad_ref, dtype)
