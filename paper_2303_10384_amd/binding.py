@@ -93,6 +93,13 @@ def load_library():
     lib.rnnt_arc_loss.restype = ctypes.c_int
     lib.rnnt_arc_loss_timed.argtypes = [vp, Shape, vp, vp, ctypes.POINTER(ArcPlanDesc), vp, vp, vp, vp, sz, vp, vp]
     lib.rnnt_arc_loss_timed.restype = ctypes.c_int
+    # csrc/rnnt_step.h: the autograd wrapper's two calls
+    lib.rnnt_step_workspace_bytes.argtypes = [Shape]
+    lib.rnnt_step_workspace_bytes.restype = sz
+    lib.rnnt_step_forward.argtypes = [vp, Shape, vp, vp, vp, i32, ctypes.c_int, vp, vp, vp, sz, vp]
+    lib.rnnt_step_forward.restype = ctypes.c_int
+    lib.rnnt_step_gradient.argtypes = [vp, Shape, i32, vp, vp, i32, ctypes.c_float, vp, vp]
+    lib.rnnt_step_gradient.restype = ctypes.c_int
     lib.rnnt_status_string.argtypes = [ctypes.c_int]
     lib.rnnt_status_string.restype = ctypes.c_char_p
     lib.rnnt_version.argtypes = []
@@ -148,6 +155,62 @@ def shape_of(logits, grad_dtype=None):
 
 def loss_workspace_bytes(B, T_max, U_max, V, dtype_code_=DTYPE_F32):
     return load_library().rnnt_loss_workspace_bytes(Shape(B, T_max, U_max, V, dtype_code_, dtype_code_))
+
+
+def _check_loss_inputs(logits, labels, logit_lens, label_lens, variant, grad_dtype=None):
+    """The checks every loss call makes on its inputs; returns their Shape."""
+    torch = _torch()
+    _check_gpu("logits", logits)
+    _check_gpu("labels", labels, torch.int32)
+    _check_gpu("logit_lens", logit_lens, torch.int32)
+    _check_gpu("label_lens", label_lens, torch.int32)
+    if logits.dim() != 4:
+        raise ValueError("logits must be (B, T_max, U_max+1, V)")
+    shape = shape_of(logits, grad_dtype)
+    if labels.shape != (shape.B, shape.U_max) or logit_lens.shape != (shape.B,) or label_lens.shape != (shape.B,):
+        raise ValueError("labels must be (B, U_max) and the length vectors (B,)")
+    if variant not in VARIANTS:
+        raise ValueError("variant must be one of %s" % sorted(VARIANTS))
+    return shape
+
+
+def step_forward(logits, labels, logit_lens, label_lens, blank, variant):
+    """Losses (B,) float32 and the row records that step_gradient forms the gradient from
+    (int32, 4 per logits row)."""
+    torch = _torch()
+    lib = load_library()
+    shape = _check_loss_inputs(logits, labels, logit_lens, label_lens, variant)
+    dev = logits.device
+    loss = torch.empty(shape.B, dtype=torch.float32, device=dev)
+    rows = torch.empty((logits.numel() // shape.V, 4), dtype=torch.int32, device=dev)
+    # from torch's allocator, ordered on the current stream like the kernels that use it
+    workspace = torch.empty(lib.rnnt_step_workspace_bytes(shape), dtype=torch.uint8, device=dev)
+    st = lib.rnnt_step_forward(_ptr(logits), shape, _ptr(labels), _ptr(logit_lens), _ptr(label_lens), int(blank),
+                               VARIANTS[variant], _ptr(loss), _ptr(rows), _ptr(workspace), workspace.numel(),
+                               _stream_handle(dev))
+    if st != RNNT_OK:
+        raise RNNTError(st, "rnnt_loss")
+    return loss, rows
+
+
+def step_gradient(logits, rows, blank, scale=None, divisor=1.0):
+    """The gradient in the logits' type, times scale / divisor: scale float32 on the GPU, of
+    one element or one per utterance, or None."""
+    torch = _torch()
+    lib = load_library()
+    _check_gpu("logits", logits)
+    shape = shape_of(logits)
+    grad = torch.empty(logits.shape, dtype=logits.dtype, device=logits.device)
+    if scale is not None:
+        _check_gpu("scale", scale, torch.float32)
+        if scale.numel() not in (1, shape.B):
+            raise ValueError("scale must hold one value or one per utterance")
+    st = lib.rnnt_step_gradient(_ptr(logits), shape, int(blank), _ptr(rows), _ptr(scale),
+                                int(scale is not None and scale.numel() != 1), float(divisor), _ptr(grad),
+                                _stream_handle(logits.device))
+    if st != RNNT_OK:
+        raise RNNTError(st, "rnnt_loss")
+    return grad
 
 
 def rnnt_loss(logits, labels, logit_lens, label_lens, blank=0, variant="rnnt", need_grad=True,

@@ -9,6 +9,7 @@
 
 #include "rnnt_mi355x.h"
 #include "rnnt_launch.h"
+#include "rnnt_step.h"
 
 // Workspace of rnnt_loss_noalloc: one copy on every GPU the library runs on.  In
 // host code this name is only a stand-in for the array; its device address is
@@ -259,6 +260,95 @@ rnnt_status_t noalloc_scratch(hipStream_t stream, void** out) {
   return RNNT_OK;
 }
 
+// Kernels 1, 2 and, when `rows` is given, 2b: losses and row records.  `ws` is the workspace
+// of layout L (its rowinfo piece is not touched unless `rows` points there).  Records
+// events[0..3] when given.
+rnnt_status_t run_rows(const void* logits, const rnnt_shape_t& shape, const int32_t* labels,
+                       const int32_t* logit_lens, const int32_t* label_lens, int32_t blank, int variant,
+                       float* loss_out, char* ws, const Layout& L, RowInfo* rows, bool keep, hipStream_t stream,
+                       hipEvent_t* events) {
+  const int64_t U1 = shape.U_max + 1;
+  const int64_t n_rows = static_cast<int64_t>(shape.B) * shape.T_max * U1;
+  const int64_t n_elem = n_rows * shape.V;
+  auto mark = [&](int i) { return events ? hipEventRecord(events[i], stream) : hipSuccess; };
+  if (mark(0) != hipSuccess) return RNNT_ERR_HIP;
+
+  // kernel 1: lse and arc weights in the lattice form
+  PopulateParams p1{};
+  p1.logits = logits;
+  p1.B = shape.B;
+  p1.T_max = shape.T_max;
+  p1.U_max = shape.U_max;
+  p1.V = shape.V;
+  p1.blank = blank;
+  p1.labels = labels;
+  p1.logit_lens = logit_lens;
+  p1.label_lens = label_lens;
+  p1.n_elem = n_elem;
+  p1.lp2 = reinterpret_cast<double2*>(ws + L.lp2);
+  p1.keep_logits = keep;
+  p1.pack_lse2f = 1;  // the posterior kernel reads lse2f from the weights
+  if (launch_populate_lattice(shape.dtype, p1, stream) != hipSuccess) return RNNT_ERR_HIP;
+  if (mark(1) != hipSuccess) return RNNT_ERR_HIP;
+
+  // kernel 2: forward / backward sweeps
+  LatticeParams p2{};
+  p2.B = shape.B;
+  p2.T_max = shape.T_max;
+  p2.U_max = shape.U_max;
+  p2.V = shape.V;
+  p2.blank = blank;
+  p2.labels = labels;
+  p2.logit_lens = logit_lens;
+  p2.label_lens = label_lens;
+  p2.lp2 = p1.lp2;
+  p2.alpha = reinterpret_cast<double*>(ws + L.alpha);
+  p2.beta = reinterpret_cast<double*>(ws + L.beta);
+  p2.u_pad = 64 * units_per_lane(shape.U_max + 1);
+  p2.lnp2_fwd = reinterpret_cast<double*>(ws + L.lnp);
+  p2.lnp2_bwd = p2.lnp2_fwd + shape.B;
+  p2.status = reinterpret_cast<int32_t*>(ws + L.status);
+  p2.loss_f32 = loss_out;
+  const hipError_t e2 = rows ? launch_lattice_scores(variant, p2, stream) : launch_lattice_loss_only(variant, p2, stream);
+  if (e2 != hipSuccess) return RNNT_ERR_HIP;
+  if (mark(2) != hipSuccess) return RNNT_ERR_HIP;
+
+  if (rows) {
+    // kernel 2b: arc posteriors -> row records
+    PostParams pb{};
+    pb.B = shape.B;
+    pb.T_max = shape.T_max;
+    pb.U_max = shape.U_max;
+    pb.labels = labels;
+    pb.logit_lens = logit_lens;
+    pb.label_lens = label_lens;
+    pb.status = p2.status;
+    pb.lp2 = p1.lp2;
+    pb.alpha = p2.alpha;
+    pb.beta = p2.beta;
+    pb.u_pad = p2.u_pad;
+    pb.lnp2_fwd = p2.lnp2_fwd;
+    pb.lnp2_bwd = p2.lnp2_bwd;
+    pb.n_rows = n_rows;
+    pb.rowinfo = rows;
+    if (launch_posteriors_rows(pb, stream) != hipSuccess) return RNNT_ERR_HIP;
+  }
+  return mark(3) == hipSuccess ? RNNT_OK : RNNT_ERR_HIP;
+}
+
+GradParams grad_params(const void* logits, const rnnt_shape_t& shape, int32_t blank, const RowInfo* rows, void* grad) {
+  GradParams p{};
+  p.logits = logits;
+  p.grad = grad;
+  p.rowinfo = rows;
+  p.n_rows = static_cast<int64_t>(shape.B) * shape.T_max * (shape.U_max + 1);
+  p.n_elem = p.n_rows * shape.V;
+  p.V = shape.V;
+  p.inv_V = 1.0 / shape.V;
+  p.blank = blank;
+  return p;
+}
+
 }  // namespace
 }  // namespace rnnt
 
@@ -314,86 +404,15 @@ rnnt_status_t rnnt_loss_timed(const void* logits, rnnt_shape_t shape, const int3
   st = take_workspace(workspace, workspace_bytes, L.total, stream, owned, &ws);
   if (st != RNNT_OK) return st;
 
-  const int64_t U1 = shape.U_max + 1;
-  const int64_t n_rows = static_cast<int64_t>(shape.B) * shape.T_max * U1;
-  const int64_t n_elem = n_rows * shape.V;
   const bool need_grad = grad_out != nullptr;
+  RowInfo* rows = need_grad ? reinterpret_cast<RowInfo*>(ws + L.rowinfo) : nullptr;
   auto mark = [&](int i) { return events ? hipEventRecord(events[i], stream) : hipSuccess; };
-  if (mark(0) != hipSuccess) return RNNT_ERR_HIP;
-
-  // kernel 1: lse and arc weights in the lattice form
-  PopulateParams p1{};
-  p1.logits = logits;
-  p1.B = shape.B;
-  p1.T_max = shape.T_max;
-  p1.U_max = shape.U_max;
-  p1.V = shape.V;
-  p1.blank = blank;
-  p1.labels = labels;
-  p1.logit_lens = logit_lens;
-  p1.label_lens = label_lens;
-  p1.n_elem = n_elem;
-  p1.lp2 = reinterpret_cast<double2*>(ws + L.lp2);
-  p1.keep_logits = keep_logits(shape, need_grad);
-  p1.pack_lse2f = 1;  // the posterior kernel reads lse2f from the weights
-  if (launch_populate_lattice(shape.dtype, p1, stream) != hipSuccess) return RNNT_ERR_HIP;
-  if (mark(1) != hipSuccess) return RNNT_ERR_HIP;
-
-  // kernel 2: forward / backward sweeps
-  LatticeParams p2{};
-  p2.B = shape.B;
-  p2.T_max = shape.T_max;
-  p2.U_max = shape.U_max;
-  p2.V = shape.V;
-  p2.blank = blank;
-  p2.labels = labels;
-  p2.logit_lens = logit_lens;
-  p2.label_lens = label_lens;
-  p2.lp2 = p1.lp2;
-  p2.alpha = reinterpret_cast<double*>(ws + L.alpha);
-  p2.beta = reinterpret_cast<double*>(ws + L.beta);
-  p2.u_pad = 64 * units_per_lane(shape.U_max + 1);
-  p2.lnp2_fwd = reinterpret_cast<double*>(ws + L.lnp);
-  p2.lnp2_bwd = p2.lnp2_fwd + shape.B;
-  p2.status = reinterpret_cast<int32_t*>(ws + L.status);
-  p2.loss_f32 = loss_out;
-  const hipError_t e2 = need_grad ? launch_lattice_scores(variant, p2, stream) : launch_lattice_loss_only(variant, p2, stream);
-  if (e2 != hipSuccess) return RNNT_ERR_HIP;
-  if (mark(2) != hipSuccess) return RNNT_ERR_HIP;
-
-  if (need_grad) {
-    // kernel 2b: arc posteriors -> row records
-    PostParams pb{};
-    pb.B = shape.B;
-    pb.T_max = shape.T_max;
-    pb.U_max = shape.U_max;
-    pb.labels = labels;
-    pb.logit_lens = logit_lens;
-    pb.label_lens = label_lens;
-    pb.status = p2.status;
-    pb.lp2 = p1.lp2;
-    pb.alpha = p2.alpha;
-    pb.beta = p2.beta;
-    pb.u_pad = p2.u_pad;
-    pb.lnp2_fwd = p2.lnp2_fwd;
-    pb.lnp2_bwd = p2.lnp2_bwd;
-    pb.n_rows = n_rows;
-    pb.rowinfo = reinterpret_cast<RowInfo*>(ws + L.rowinfo);
-    if (launch_posteriors_rows(pb, stream) != hipSuccess) return RNNT_ERR_HIP;
-  }
-  if (mark(3) != hipSuccess) return RNNT_ERR_HIP;
-
+  st = run_rows(logits, shape, labels, logit_lens, label_lens, blank, variant, loss_out, ws, L, rows,
+                keep_logits(shape, need_grad), stream, events);
+  if (st != RNNT_OK) return st;
   if (need_grad) {
     // kernel 3: gradient
-    GradParams p3{};
-    p3.logits = logits;
-    p3.grad = grad_out;
-    p3.rowinfo = reinterpret_cast<RowInfo*>(ws + L.rowinfo);
-    p3.n_elem = n_elem;
-    p3.n_rows = n_rows;
-    p3.V = shape.V;
-    p3.inv_V = 1.0 / shape.V;
-    p3.blank = blank;
+    const GradParams p3 = grad_params(logits, shape, blank, rows, grad_out);
     if (launch_grad(shape.dtype, shape.grad_dtype, p3, stream) != hipSuccess) return RNNT_ERR_HIP;
   }
   if (mark(4) != hipSuccess) return RNNT_ERR_HIP;
@@ -406,6 +425,47 @@ rnnt_status_t rnnt_loss(const void* logits, rnnt_shape_t shape, const int32_t* l
                         size_t workspace_bytes, hipStream_t stream) {
   return rnnt_loss_timed(logits, shape, labels, logit_lens, label_lens, blank, variant, loss_out, grad_out,
                          workspace, workspace_bytes, stream, nullptr);
+}
+
+size_t rnnt_step_workspace_bytes(rnnt_shape_t shape) {
+  if (check_shape(shape) != RNNT_OK) return 0;
+  const Layout L = make_layout(shape, true);
+  return L.total - L.lp2;
+}
+
+rnnt_status_t rnnt_step_forward(const void* logits, rnnt_shape_t shape, const int32_t* labels,
+                                const int32_t* logit_lens, const int32_t* label_lens, int32_t blank,
+                                rnnt_variant_t variant, float* loss_out, void* rows_out, void* workspace,
+                                size_t workspace_bytes, hipStream_t stream) {
+  const rnnt_status_t st = check_loss_args(logits, shape, labels, logit_lens, label_lens, blank, variant, loss_out,
+                                           nullptr);
+  if (st != RNNT_OK) return st;
+  if (!rows_out || !workspace) return RNNT_ERR_NULL_PTR;
+  if (!aligned16(rows_out) || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return RNNT_ERR_ALIGNMENT;
+  const Layout L = make_layout(shape, true);
+  if (workspace_bytes < L.total - L.lp2) return RNNT_ERR_WORKSPACE;
+  // the row records live in rows_out: the workspace is the layout from lp2 on
+  return run_rows(logits, shape, labels, logit_lens, label_lens, blank, variant, loss_out,
+                  static_cast<char*>(workspace) - L.lp2, L, static_cast<RowInfo*>(rows_out), keep_logits(shape, true),
+                  stream, nullptr);
+}
+
+rnnt_status_t rnnt_step_gradient(const void* logits, rnnt_shape_t shape, int32_t blank, const void* rows,
+                                 const float* scale, int32_t scale_per_utterance, float divisor, void* grad_out,
+                                 hipStream_t stream) {
+  const rnnt_status_t st = check_shape(shape);
+  if (st != RNNT_OK) return st;
+  if (!logits || !rows || !grad_out) return RNNT_ERR_NULL_PTR;
+  if (shape.grad_dtype != shape.dtype) return RNNT_ERR_BAD_DTYPE;
+  if (blank < 0 || blank >= shape.V) return RNNT_ERR_BAD_BLANK;
+  if (!aligned16(logits) || !aligned16(grad_out) || !aligned16(rows)) return RNNT_ERR_ALIGNMENT;
+  GradParams p = grad_params(logits, shape, blank, static_cast<const RowInfo*>(rows), grad_out);
+  p.scale = scale;
+  p.scale_stride = scale_per_utterance ? 1 : 0;
+  p.divisor = divisor;
+  p.rows_per_utt = shape.T_max * (shape.U_max + 1);
+  p.inv_rows_per_utt = 1.0 / p.rows_per_utt;
+  return launch_grad(shape.dtype, shape.grad_dtype, p, stream) == hipSuccess ? RNNT_OK : RNNT_ERR_HIP;
 }
 
 rnnt_status_t rnnt_loss_noalloc(const void* logits, rnnt_shape_t shape, const int32_t* labels,
@@ -618,15 +678,7 @@ rnnt_status_t rnnt_arc_loss_timed(const void* logits, rnnt_shape_t shape, const 
   if (mark(4) != hipSuccess) return RNNT_ERR_HIP;
 
   if (grad_out) {
-    GradParams p3{};
-    p3.logits = logits;
-    p3.grad = grad_out;
-    p3.rowinfo = pr.rowinfo;
-    p3.n_elem = n_rows * shape.V;
-    p3.n_rows = n_rows;
-    p3.V = shape.V;
-    p3.inv_V = 1.0 / shape.V;
-    p3.blank = plan->blank;
+    const GradParams p3 = grad_params(logits, shape, plan->blank, pr.rowinfo, grad_out);
     if (launch_grad(shape.dtype, shape.grad_dtype, p3, stream) != hipSuccess) return RNNT_ERR_HIP;
     ArcExtraParams px{};
     px.rows = pr;

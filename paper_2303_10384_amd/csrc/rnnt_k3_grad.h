@@ -34,6 +34,13 @@ struct GradParams {
   int64_t n_rows;  // B * T_max * (U_max+1)
   int32_t V, blank;
   double inv_V;  // 1 / V, rounded
+  // upstream gradient (the SCALED kernels): every element of utterance b is multiplied by
+  // scale[b * scale_stride] / divisor, zero rows included
+  const float* scale;
+  int32_t scale_stride;   // 1 (a gradient per utterance) or 0 (one of the reduced loss)
+  float divisor;          // the batch for a mean, else 1
+  int32_t rows_per_utt;   // T_max * (U_max+1)
+  double inv_rows_per_utt;
 };
 
 constexpr int kGradChunksPerThread = 2;
@@ -105,6 +112,17 @@ __device__ __forceinline__ void split_row(int64_t e, int V, double inv_V, int64_
   col = __builtin_amdgcn_readfirstlane(static_cast<int>(r));
 }
 
+// The upstream factor of row r (a row past the end takes the last utterance's).
+__device__ __forceinline__ float row_scale(const GradParams& p, int64_t r) {
+  int64_t b = 0;
+  if (p.scale_stride != 0) {
+    b = static_cast<int64_t>(static_cast<double>(r) * p.inv_rows_per_utt);  // at most one off, as in split_row
+    const int64_t rest = r - b * p.rows_per_utt;
+    b += rest < 0 ? -1 : rest >= p.rows_per_utt ? 1 : 0;
+  }
+  return p.scale[b] / p.divisor;
+}
+
 __device__ __forceinline__ float grad_elem(float z, int v, const RowInfo& ri, int blank) {
   const float pr = fast_exp2(fmaf(z, kLog2eF, -ri.lse2));
   float g = pr * (ri.occ_blank + ri.occ_label);
@@ -125,7 +143,7 @@ __device__ __forceinline__ void store_chunk(void* dst, int64_t e0, const float* 
 // so one chunk may cover several rows.  Only small-V tensors and the block
 // holding the final partial chunk come here; zero rows' logits are read too
 // (and ignored).
-template <typename T, typename Tout, bool SMALLV>
+template <typename T, typename Tout, bool SMALLV, bool SCALED>
 __device__ __forceinline__ void grad_chunks_general(const GradParams& p, int64_t tile0, int64_t r_tile,
                                                     uint32_t v_tile) {
   constexpr int EPC = kGradEpc<T, Tout>;
@@ -145,6 +163,7 @@ __device__ __forceinline__ void grad_chunks_general(const GradParams& p, int64_t
     const bool full = e0 + EPC <= p.n_elem;
     float f[EPC], out[EPC];
     RowInfo ri = p.rowinfo[r];
+    float up = SCALED ? row_scale(p, r) : 1.f;
     if (full) {
       LogitChunk<T, EPC> z;
       z.template load<kK3StreamLoads>(src_e + e0);
@@ -158,9 +177,13 @@ __device__ __forceinline__ void grad_chunks_general(const GradParams& p, int64_t
       if (v >= p.V) {  // next row (at most once per chunk unless SMALLV)
         v -= p.V;
         ++r;
-        if (r < p.n_rows) ri = p.rowinfo[r];
+        if (r < p.n_rows) {
+          ri = p.rowinfo[r];
+          if (SCALED) up = row_scale(p, r);
+        }
       }
       out[j] = grad_elem(f[j], v, ri, p.blank);
+      if (SCALED) out[j] *= up;
       ++v;
     }
     if (full) {
@@ -181,7 +204,10 @@ __device__ __forceinline__ void grad_chunks_general(const GradParams& p, int64_t
 // unconditionally (a chunk whose logits are not needed gets an offset past the
 // buffer's end, which reads zero without touching memory); arithmetic and
 // stores.
-template <typename Tin, typename Tout, bool SMALLV>
+// SCALED: the gradient of a loss that other operations follow (the autograd wrapper's
+// backward): each element is multiplied by its utterance's upstream gradient before it is
+// stored, in place of passes over the whole gradient afterwards.
+template <typename Tin, typename Tout, bool SMALLV, bool SCALED = false>
 __global__ __launch_bounds__(kGradThreads<Tout>) void k3_grad(GradParams p) {
   using T = Tin;
   constexpr int EPC = kGradEpc<Tin, Tout>;
@@ -198,7 +224,7 @@ __global__ __launch_bounds__(kGradThreads<Tout>) void k3_grad(GradParams p) {
   const uint32_t uV = static_cast<uint32_t>(p.V);
   const int64_t n_full = p.n_elem / EPC;  // chunks wholly inside the tensor
   if (SMALLV || (p.n_elem % EPC != 0 && tile0 + kTile > n_full)) {
-    grad_chunks_general<T, Tout, SMALLV>(p, tile0, r_tile, v_tile);
+    grad_chunks_general<T, Tout, SMALLV, SCALED>(p, tile0, r_tile, v_tile);
     return;
   }
 
@@ -249,6 +275,11 @@ __global__ __launch_bounds__(kGradThreads<Tout>) void k3_grad(GradParams p) {
     } else {  // the wave's chunks q all lie in zero rows (padding, bad utterances)
 #pragma unroll
       for (int j = 0; j < EPC; ++j) out[j] = 0.f;
+    }
+    if constexpr (SCALED) {
+      const float up0 = row_scale(p, r[q]), up1 = row_scale(p, min(r[q] + 1, p.n_rows - 1));
+#pragma unroll
+      for (int j = 0; j < EPC; ++j) out[j] *= v[q] + j >= p.V ? up1 : up0;
     }
     if (store[q]) store_chunk<Tout, EPC>(p.grad, (tile0 + q * kThreads + static_cast<int>(threadIdx.x)) * EPC, out);
   }
@@ -310,7 +341,7 @@ __device__ __forceinline__ bool one_exp_shift(const RowInfo& r, float& s, float&
   return one;
 }
 
-template <typename Tin, typename Tout>
+template <typename Tin, typename Tout, bool SCALED = false>
 __global__ __launch_bounds__(kGradThreads<Tout>) void k3_grad_wide(GradParams p) {
   using T = Tin;
   constexpr int EPC = kGradEpc<Tin, Tout>;
@@ -325,7 +356,7 @@ __global__ __launch_bounds__(kGradThreads<Tout>) void k3_grad_wide(GradParams p)
   split_row(e_tile, p.V, p.inv_V, r_tile, v_tile);
   const int64_t n_full = p.n_elem / EPC;  // chunks wholly inside the tensor
   if (p.n_elem % EPC != 0 && tile0 + kTile > n_full) {
-    grad_chunks_general<T, Tout, false>(p, tile0, r_tile, static_cast<uint32_t>(v_tile));
+    grad_chunks_general<T, Tout, false, SCALED>(p, tile0, r_tile, static_cast<uint32_t>(v_tile));
     return;
   }
   const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
@@ -335,6 +366,7 @@ __global__ __launch_bounds__(kGradThreads<Tout>) void k3_grad_wide(GradParams p)
   // group q of this wave: chunks tile0 + q*kThreads + 64*wave + lane; its first
   // element is column va of row ra (wave-uniform)
   int va[Q];
+  int64_t row_a[SCALED ? Q : 1];
   RowInfo Ra[Q], Rb[Q];
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
@@ -342,6 +374,7 @@ __global__ __launch_bounds__(kGradThreads<Tout>) void k3_grad_wide(GradParams p)
     const int dr = off / p.V;
     va[q] = off - dr * p.V;
     const int64_t ra = min(r_tile + dr, p.n_rows - 1);  // groups past the end store nothing
+    if (SCALED) row_a[q] = ra;
     Ra[q] = rows[ra];
     Rb[q] = rows[min(ra + 1, p.n_rows - 1)];
   }
@@ -410,6 +443,19 @@ __global__ __launch_bounds__(kGradThreads<Tout>) void k3_grad_wide(GradParams p)
       if (!zb && to_b < kWave * EPC) {
         fix_column<EPC>(out, lane, to_b + p.blank, Rb[q].occ_blank);
         if (Rb[q].label >= 0) fix_column<EPC>(out, lane, to_b + Rb[q].label, Rb[q].occ_label);
+      }
+    }
+    if constexpr (SCALED) {
+      const float up_a = row_scale(p, row_a[q]);
+      if (to_b >= kWave * EPC || p.scale_stride == 0) {
+#pragma unroll
+        for (int j = 0; j < EPC; ++j) out[j] *= up_a;
+      } else {  // row b's elements, as above
+        const float up_b = row_scale(p, min(row_a[q] + 1, p.n_rows - 1));
+        const int L = to_b / EPC, ks = to_b % EPC;
+        const float up_lo = lane > L ? up_b : up_a, up_hi = lane >= L ? up_b : up_a;
+#pragma unroll
+        for (int j = 0; j < EPC; ++j) out[j] *= j < ks ? up_lo : up_hi;
       }
     }
     if (tile0 + cl < n_full) store_chunk<Tout, EPC>(p.grad, (tile0 + cl) * EPC, out);

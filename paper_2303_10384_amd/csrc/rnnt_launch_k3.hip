@@ -10,30 +10,38 @@ namespace {
 
 // ---- kernel 3 ---------------------------------------------------------------
 
-template <typename Tin, typename Tout>
+template <typename Tin, typename Tout, bool SCALED>
 hipError_t launch_k3(const GradParams& p, hipStream_t stream) {
   constexpr int EPC = kGradEpc<Tin, Tout>;
   const int64_t chunks = (p.n_elem + EPC - 1) / EPC;
   const int64_t blocks = (chunks + kGradTileChunks<Tout> - 1) / kGradTileChunks<Tout>;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+  const dim3 grid(static_cast<uint32_t>(blocks)), block(kGradThreads<Tout>);
   if (p.V < EPC)
-    hipLaunchKernelGGL((k3_grad<Tin, Tout, true>), dim3(static_cast<uint32_t>(blocks)), dim3(kGradThreads<Tout>), 0,
-                       stream, p);
+    hipLaunchKernelGGL((k3_grad<Tin, Tout, true, SCALED>), grid, block, 0, stream, p);
   else if (p.V >= kWideMinV<Tin, Tout>)
-    hipLaunchKernelGGL((k3_grad_wide<Tin, Tout>), dim3(static_cast<uint32_t>(blocks)), dim3(kGradThreads<Tout>), 0,
-                       stream, p);
+    hipLaunchKernelGGL((k3_grad_wide<Tin, Tout, SCALED>), grid, block, 0, stream, p);
   else
-    hipLaunchKernelGGL((k3_grad<Tin, Tout, false>), dim3(static_cast<uint32_t>(blocks)), dim3(kGradThreads<Tout>), 0,
-                       stream, p);
+    hipLaunchKernelGGL((k3_grad<Tin, Tout, false, SCALED>), grid, block, 0, stream, p);
   return hipGetLastError();
 }
 
 hipError_t launch_k3_dtype(rnnt_dtype_t dt, rnnt_dtype_t gdt, const GradParams& p, hipStream_t stream) {
   const bool f32_out = gdt == RNNT_DTYPE_F32;
   switch (dt) {
-    case RNNT_DTYPE_F32: return launch_k3<float, float>(p, stream);
-    case RNNT_DTYPE_BF16: return f32_out ? launch_k3<bf16_t, float>(p, stream) : launch_k3<bf16_t, bf16_t>(p, stream);
-    default: return f32_out ? launch_k3<f16_t, float>(p, stream) : launch_k3<f16_t, f16_t>(p, stream);
+    case RNNT_DTYPE_F32: return launch_k3<float, float, false>(p, stream);
+    case RNNT_DTYPE_BF16:
+      return f32_out ? launch_k3<bf16_t, float, false>(p, stream) : launch_k3<bf16_t, bf16_t, false>(p, stream);
+    default: return f32_out ? launch_k3<f16_t, float, false>(p, stream) : launch_k3<f16_t, f16_t, false>(p, stream);
+  }
+}
+
+// with an upstream gradient: stored in the logits' type
+hipError_t launch_k3_scaled(rnnt_dtype_t dt, const GradParams& p, hipStream_t stream) {
+  switch (dt) {
+    case RNNT_DTYPE_F32: return launch_k3<float, float, true>(p, stream);
+    case RNNT_DTYPE_BF16: return launch_k3<bf16_t, bf16_t, true>(p, stream);
+    default: return launch_k3<f16_t, f16_t, true>(p, stream);
   }
 }
 
@@ -95,7 +103,7 @@ hipError_t launch_extra_rows(rnnt_dtype_t dt, rnnt_dtype_t gdt, const ArcExtraPa
 }  // namespace
 
 hipError_t launch_grad(rnnt_dtype_t dt, rnnt_dtype_t gdt, const GradParams& p, hipStream_t stream) {
-  return launch_k3_dtype(dt, gdt, p, stream);
+  return p.scale ? launch_k3_scaled(dt, p, stream) : launch_k3_dtype(dt, gdt, p, stream);
 }
 
 hipError_t launch_arc_sweep(int ns, int dm, const ArcSweepParams& p, hipStream_t stream) {

@@ -1,0 +1,71 @@
+"""RNNTLoss backward: the gradient kernel's upstream factor against the plain gradient of
+rnnt_loss times the factor, for every form of the kernel (rows shorter than a chunk, short
+rows, rows of at least 64 chunks), reduction and dtype."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2303_10384_amd import workloads as W
+from test_gpu_parity import pkg, to_dev, torch  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def announce(request):
+    sys.__stderr__.write("\n[gpu-test] %s\n" % request.node.nodeid)
+    sys.__stderr__.flush()
+    yield
+
+
+def make(torch, V, dtype, bad=False):  # noqa: F811
+    logits, tl, ul, labels = W.small_case(5, 7, 6, V, 40 + V)
+    if bad:
+        tl[2] = 0
+    x = to_dev(torch, logits).to(W.torch_dtype(dtype))
+    return x, to_dev(torch, labels), to_dev(torch, tl), to_dev(torch, ul)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("V", [3, 30, 257, 515])
+@pytest.mark.parametrize("reduction", ["none", "sum", "mean"])
+def test_upstream_gradient(torch, pkg, V, dtype, reduction):  # noqa: F811
+    x, y, tl, ul = make(torch, V, dtype, bad=True)
+    _, g = pkg.rnnt_loss(x, y, tl, ul, variant="wrnnt", grad_dtype=torch.float32)
+    xr = x.clone().requires_grad_(True)
+    loss = pkg.RNNTLoss(0, "wrnnt", reduction)(xr, y, tl, ul)
+    up = torch.tensor([0.5, -3.0, 2.0, 0.0, 65536.0], device="cuda") if reduction == "none" else \
+        torch.tensor(-0.75, device="cuda")
+    got = [torch.autograd.grad(loss, xr, up, retain_graph=True)[0] for _ in range(2)]
+    assert torch.equal(got[0], got[1])  # a second backward over a kept graph
+    factor = up.view(-1, 1, 1, 1) if reduction == "none" else up / 5 if reduction == "mean" else up
+    ref = (g.double() * factor.double()).cpu().numpy()
+    out = got[0].double().cpu().numpy()
+    # the same float32 arithmetic, the product rounded in float32 and once more when stored
+    ulp = {"f32": 2.0 ** -23, "bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype]
+    tiny = {"f32": 1e-30, "bf16": 1e-30, "f16": 2.0 ** -24}[dtype]
+    scale = np.abs(factor.cpu().numpy())
+    with np.errstate(invalid="ignore"):
+        bad = ~(np.abs(out - ref) <= ulp * np.abs(ref) + 2.0 ** -23 * scale + tiny)
+    if dtype == "f16":
+        bad &= np.abs(ref) < 65000.0
+    assert not bad.any(), np.argwhere(bad)[:5]
+    assert np.all(out[2] == 0)  # the bad utterance
+
+
+def test_create_graph_and_repeated_training_steps(torch, pkg):  # noqa: F811
+    x, y, tl, ul = make(torch, 33, "f32")
+    xr = x.clone().requires_grad_(True)
+    w = torch.tensor(2.0, device="cuda", requires_grad=True)
+    (g,) = torch.autograd.grad(w * pkg.rnnt_loss_autograd(xr, y, tl, ul, reduction="sum"), xr, create_graph=True)
+    (dw,) = torch.autograd.grad(g.sum() + (g * g).sum(), w)  # g is linear in w
+    _, plain = pkg.rnnt_loss(x, y, tl, ul)
+    want = plain.double().sum() + 4.0 * (plain.double() ** 2).sum()
+    assert abs(float(dw) - float(want)) <= 1e-4 * abs(float(want)) + 1e-4
+    for _ in range(2):  # accumulation into .grad
+        pkg.RNNTLoss(reduction="sum")(xr, y, tl, ul).backward()
+    assert torch.allclose(xr.grad, 2 * plain, rtol=1e-6, atol=1e-7)
+    with torch.no_grad():
+        loss = pkg.RNNTLoss(reduction="none")(xr, y, tl, ul)
+    assert not loss.requires_grad and torch.equal(loss, pkg.rnnt_loss(x, y, tl, ul, need_grad=False)[0])
