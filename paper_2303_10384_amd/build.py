@@ -20,7 +20,7 @@ SOURCES = ["csrc/rnnt_api.hip", "csrc/rnnt_launch_k1_lattice.hip", "csrc/rnnt_la
            "csrc/rnnt_launch_k1_dense.hip", "csrc/rnnt_launch_k2_scores.hip", "csrc/rnnt_launch_k2_loss.hip",
            "csrc/rnnt_launch_k2_dense.hip", "csrc/rnnt_launch_viterbi.hip", "csrc/rnnt_launch_k3.hip",
            "csrc/rnnt_arc_plan.cpp"]
-HEADERS = ["csrc/rnnt_device.h", "csrc/rnnt_k1_populate.h", "csrc/rnnt_k2_lattice.h", "csrc/rnnt_k2_viterbi.h",
+HEADERS = ["csrc/rnnt_device.h", "csrc/rnnt_k1_populate.h", "csrc/rnnt_k2_lattice.h", "csrc/rnnt_k2_linear.h", "csrc/rnnt_k2_viterbi.h",
            "csrc/rnnt_k3_grad.h", "csrc/rnnt_arc_layout.h", "csrc/rnnt_arc_kernels.h", "csrc/rnnt_launch.h", "csrc/rnnt_step.h",
            "csrc/rnnt_launch_k1.h", "csrc/rnnt_launch_k2.h"]
 

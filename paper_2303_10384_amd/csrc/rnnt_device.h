@@ -61,6 +61,7 @@ struct LatticeRecordSrc {
   const double* alpha;          // (B, T_max+U_max+1, u_pad) by diagonal, log2 units
   const double* beta;
   const double* lnp2_fwd;       // (B) log2 P
+  int32_t log2_alpha, log2_beta;  // linear sweeps: the utterance's array holds log2 scores
 };
 
 // Lattice scores are kept in log2 units (x * log2 e).  An absent arc, and a
@@ -84,12 +85,33 @@ __device__ __forceinline__ double log_add2(double x, double y) {
   return m + static_cast<double>(c);
 }
 
+// ---- weights and scores of the linear sweeps (rnnt_k2_linear.h)
+// A weight x (log2 units) as a probability, or as x itself (negative) below 2^-kLinearMinLog2;
+// an absent arc is 0.  Both carry lse2f in their low 16 bits like the log2 form; the bits make
+// 0 a subnormal below 2^-1056.
+constexpr double kLinearMinLog2 = 200.0;
+__device__ __forceinline__ double code_weight(double x) {
+  return x >= -kLinearMinLog2 ? exp2(x) : (x < kNoArc ? kNoArc : x);  // NaN stays NaN
+}
+__device__ __forceinline__ double decode_weight(double w) {
+  return w < 0.0 ? w : w < 0x1p-1000 ? kNoArc : log2(w);
+}
+// The exponent in the low 24 bits of a stored score m * 2^E, and the score's logarithm; a score
+// of 0 carries kZeroScore.
+constexpr int kZeroScore = -(1 << 23);
+__device__ __forceinline__ int score_exp(double x) { return (__double2loint(x) << 8) >> 8; }
+__device__ __forceinline__ double score_log2(double x) {
+  const int e = score_exp(x);
+  return e == kZeroScore ? kNoArc : log2(x) + static_cast<double>(e);
+}
+
 // Row record of the valid row r = (b, t, u) (t < T, u <= U) of a good utterance:
 //   occ_blank = 2^(alpha(t,u) + lp_blank(t,u) + beta(t+1,u) - log2 P)   (t < T-1)
 //   occ_blank = 2^(alpha(T-1,U) + lp_blank(T-1,U) - log2 P)            (closing blank)
 //   occ_label = 2^(alpha(t,u) + lp_label(t,u) + beta(t,u+1) - log2 P)   (u < U)
 // and 0 for an absent arc.  Every load is issued unconditionally, at an index
 // inside the arrays (beta's unit clamped into its row).
+template <bool CODED>
 __device__ __forceinline__ RowInfo lattice_row_record(const LatticeRecordSrc& s, int b, int t, int u, int64_t r,
                                                       int T, int U, double lnP2) {
   const int d = t + u;
@@ -101,14 +123,41 @@ __device__ __forceinline__ RowInfo lattice_row_record(const LatticeRecordSrc& s,
   const double2 w = s.lp2[r];
   const float lse2 = unpack_lse2f(w);
   const int y = s.U_max > 0 ? s.labels[static_cast<int64_t>(b) * s.U_max + min(u, s.U_max - 1)] : kNoLabel;
-  double xb = kNoArc, xl = kNoArc;
-  if (t < T - 1) xb = al + w.x + b_down - lnP2;
-  else if (u == U) xb = al + w.x - lnP2;
-  if (u < U) xl = al + w.y + b_right - lnP2;
+  const bool closing = t == T - 1 && u == U;
+  const bool has_blank = t < T - 1 || closing, has_label = u < U;
   RowInfo o;
   o.lse2 = lse2;
-  o.occ_blank = fast_exp2(static_cast<float>(xb));
-  o.occ_label = fast_exp2(static_cast<float>(xl));
+  if (CODED && !(s.log2_alpha | s.log2_beta) && lnP2 > 0.5 * kNoArc && !(w.x < 0.0) && !(w.y < 0.0)) {
+    // scores m * 2^E, weights as probabilities: the product of three numbers (scores within
+    // [2^-320, 2^450] and probabilities from 2^-200, so it neither over- nor underflows) times a
+    // power of two
+    const double eP = __builtin_rint(lnP2);
+    const float fP = fast_exp2(static_cast<float>(eP - lnP2));  // 2^(eP) / P
+    const int e0 = score_exp(al) - static_cast<int>(eP);
+    auto posterior = [&](double m, int e) {  // 0 below 2^-126, like the exponential unit
+      const float x = static_cast<float>(ldexp(m, e)) * fP;
+      return x < 0x1p-126f ? 0.f : x;
+    };
+    const double down = closing ? 1.0 : b_down;
+    const int e_down = closing ? 0 : score_exp(b_down);
+    o.occ_blank = has_blank ? posterior(al * w.x * down, e0 + e_down) : 0.f;
+    o.occ_label = has_label ? posterior(al * w.y * b_right, e0 + score_exp(b_right)) : 0.f;
+  } else {
+    double la = al, ld = b_down, lr = b_right, wx = w.x, wy = w.y;
+    if (CODED) {
+      la = s.log2_alpha ? al : score_log2(al);
+      ld = s.log2_beta ? b_down : score_log2(b_down);
+      lr = s.log2_beta ? b_right : score_log2(b_right);
+      wx = decode_weight(w.x);
+      wy = decode_weight(w.y);
+    }
+    double xb = kNoArc, xl = kNoArc;
+    if (t < T - 1) xb = la + wx + ld - lnP2;
+    else if (u == U) xb = la + wx - lnP2;
+    if (u < U) xl = la + wy + lr - lnP2;
+    o.occ_blank = fast_exp2(static_cast<float>(xb));
+    o.occ_label = fast_exp2(static_cast<float>(xl));
+  }
   o.label = (u < U) ? y : kNoLabel;
   // Both posteriors underflow float32 (the node lies far from every likely path) and the
   // row's normaliser is finite, so every logit of the row is finite: its gradient

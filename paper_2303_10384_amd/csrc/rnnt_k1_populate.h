@@ -68,6 +68,7 @@ struct PopulateParams {
   int32_t rows_per_block;  // consecutive units u per block (<= kMaxRowsPerBlock)
   // lattice form
   double2* lp2;            // (B, T_max, U_max+1) {lp_blank, lp_label} * log2(e)
+  int32_t linear;          // nonzero: the weights as probabilities (code_weight), absent arcs 0
   int32_t pack_lse2f;      // nonzero: lse2f rides in the low bits of each row's two weights (the loss);
                            // zero: the weights as they are (forced alignment, whose ties stay exact)
   // dense form
@@ -610,8 +611,13 @@ __global__ __launch_bounds__(256) void k1_populate(PopulateParams p) {
     if (OUT == kK1Lattice) {
       const bool blank_arc = (t < Tb - 1) || (u == Ub);  // absent: last frame below the top row
       double2 w;
-      w.x = blank_arc ? clamp_no_arc(lpb * kLog2eD) : kNoArc;
-      w.y = (u < Ub) ? clamp_no_arc(lpl * kLog2eD) : kNoArc;
+      if (p.linear) {
+        w.x = blank_arc ? code_weight(lpb * kLog2eD) : 0.0;
+        w.y = (u < Ub) ? code_weight(lpl * kLog2eD) : 0.0;
+      } else {
+        w.x = blank_arc ? clamp_no_arc(lpb * kLog2eD) : kNoArc;
+        w.y = (u < Ub) ? clamp_no_arc(lpl * kLog2eD) : kNoArc;
+      }
       // device-scope stores, written through the L2 as they are issued: K1's
       // stream of reads then slows less than under the L2's later write-backs
       // (large bf16: K1 0.822 -> 0.812 ms); the block's rows are consecutive

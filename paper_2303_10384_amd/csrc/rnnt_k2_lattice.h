@@ -56,6 +56,13 @@ enum LatticeMode : int {
   kScores = 1,    // forward and backward waves, alpha and beta stored
 };
 
+// Form of the weights a sweep reads.
+enum WeightForm : int {
+  kWeightsLog2 = 0,   // kernel 1's lattice form in log2 units
+  kWeightsDense = 1,  // dense natural-log arrays (the lattice-only entry point)
+  kWeightsCoded = 2,  // kernel 1's lattice form as probabilities (coded_weight)
+};
+
 struct LatticeParams {
   int32_t B, T_max, U_max, V, blank;
   const int32_t* labels;  // (B, U_max) or null (lattice-only entry point)
@@ -156,16 +163,12 @@ __device__ __forceinline__ double wave_log_sum(double x) {
 // and every wave passes one barrier per segment, active or not, so every wave
 // reaches the same barriers.  One unit per lane shortens a step's dependent
 // chain to one log-add; the stagger costs NW-1 segments per sweep.
-template <int K, int PF, int VAR, int MODE, bool DENSE_IN, int NW = 1>
-__global__ __launch_bounds__(64 * NW) void k2_lattice(LatticeParams p) {
+template <int K, int PF, int VAR, int MODE, WeightForm FORM, int NW>
+__device__ __forceinline__ void lattice_sweep(const LatticeParams& p, int b, int sweep, int tid, int T, int U) {
   static_assert(NW >= 1 && NW <= 4, "one to four waves per sweep");
-  const int b = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int T = p.logit_lens[b];
-  const int U = p.label_lens[b];
+  constexpr bool DENSE_IN = FORM == kWeightsDense;
   const int U1 = p.U_max + 1;
   const int ND = p.T_max + p.U_max;  // diagonals of the lattice form
-  const double kNaN = __builtin_nan("");
   // the neighbouring wave's value of each step of a segment, two segments in turn;
   // every lane writes each step (no exec mask), the lanes without a value to pass
   // into a scratch run of their own (lane + step: no two lanes of a write collide)
@@ -175,27 +178,6 @@ __global__ __launch_bounds__(64 * NW) void k2_lattice(LatticeParams p) {
   // the sweep (alpha(d-U, U) forward, beta(d, 0) backward), one per step
   __shared__ double s_sum[VAR != 0 ? PF : 1];
 
-  bool ok = (T >= 1 && T <= p.T_max && U >= 0 && U <= p.U_max);
-  int bad = 0;
-  if (ok && p.labels != nullptr) {
-    for (int u = tid; u < U; u += blockDim.x) {
-      const int y = p.labels[static_cast<int64_t>(b) * p.U_max + u];
-      if (y < 0 || y >= p.V || y == p.blank) bad = 1;
-    }
-  }
-  bad = __syncthreads_or(bad);
-  // both sweeps of an utterance reach the same verdict and store the same values
-  if (tid == 0) p.status[b] = (ok && !bad) ? 0 : 1;
-  if (!ok || bad) {  // the whole block leaves together
-    if (tid == 0) {
-      p.lnp2_fwd[b] = kNaN;
-      p.lnp2_bwd[b] = kNaN;
-      if (p.loss_f32) p.loss_f32[b] = __builtin_nanf("");
-    }
-    return;
-  }
-
-  const int sweep = blockIdx.y;  // 0: forward, 1: backward (a block of its own)
   const int lane = tid % kWave;
   const int wv = (NW == 1) ? 0 : __builtin_amdgcn_readfirstlane(tid / kWave);
   const int ub = wv * kWave * K;  // this wave's first unit
@@ -217,8 +199,8 @@ __global__ __launch_bounds__(64 * NW) void k2_lattice(LatticeParams p) {
       const int hi = __builtin_amdgcn_readfirstlane(min(ec, U));
       const int uc = min(max(ub + lane * K + k, ec - (T - 1)), hi);
       const double2 w = load_lattice_cell(w_rsrc, 16 * ec * U1, uc, neg_step);  // row (t, u) = (ec - uc, uc)
-      wb = w.x;
-      wl = w.y;
+      wb = FORM == kWeightsCoded ? decode_weight(w.x) : w.x;
+      wl = FORM == kWeightsCoded ? decode_weight(w.y) : w.y;
     } else {
       load_cell<true>(p, b, e, ub + lane * K + k, T, U, D, wb, wl);
     }
@@ -240,6 +222,7 @@ __global__ __launch_bounds__(64 * NW) void k2_lattice(LatticeParams p) {
   double w_close, w_unused;
   if (!DENSE_IN) {
     w_close = w_utt[(T - 1) * U1 + U].x;
+    if (FORM == kWeightsCoded) w_close = decode_weight(w_close);
   } else {
     load_cell<true>(p, b, D, U, T, U, D, w_close, w_unused);
     w_close = to_lattice(w_close, true);
@@ -443,8 +426,38 @@ __global__ __launch_bounds__(64 * NW) void k2_lattice(LatticeParams p) {
         b_utt[0] = b00;
       }
     }
-    if (wv == 0 && lane == 0) p.lnp2_bwd[b] = b00;
+    if (FORM != kWeightsCoded && wv == 0 && lane == 0) p.lnp2_bwd[b] = b00;
   }
+}
+
+template <int K, int PF, int VAR, int MODE, bool DENSE_IN, int NW = 1>
+__global__ __launch_bounds__(64 * NW) void k2_lattice(LatticeParams p) {
+  const int b = blockIdx.x;
+  const int tid = threadIdx.x;
+  const int T = p.logit_lens[b];
+  const int U = p.label_lens[b];
+  const double kNaN = __builtin_nan("");
+  bool ok = (T >= 1 && T <= p.T_max && U >= 0 && U <= p.U_max);
+  int bad = 0;
+  if (ok && p.labels != nullptr) {
+    for (int u = tid; u < U; u += blockDim.x) {
+      const int y = p.labels[static_cast<int64_t>(b) * p.U_max + u];
+      if (y < 0 || y >= p.V || y == p.blank) bad = 1;
+    }
+  }
+  bad = __syncthreads_or(bad);
+  // both sweeps of an utterance reach the same verdict and store the same values
+  if (tid == 0) p.status[b] = (ok && !bad) ? 0 : 1;
+  if (!ok || bad) {  // the whole block leaves together
+    if (tid == 0) {
+      p.lnp2_fwd[b] = kNaN;
+      p.lnp2_bwd[b] = kNaN;
+      if (p.loss_f32) p.loss_f32[b] = __builtin_nanf("");
+    }
+    return;
+  }
+  // blockIdx.y: 0 forward, 1 backward (a block of its own)
+  lattice_sweep<K, PF, VAR, MODE, DENSE_IN ? kWeightsDense : kWeightsLog2, NW>(p, b, blockIdx.y, tid, T, U);
 }
 
 // ---------------------------------------------------------------------------
@@ -457,6 +470,7 @@ struct PostParams {
   const int32_t* label_lens;
   const int32_t* status;
   const double2* lp2;  // kernel 1's lattice form (lse2f in the weights' low bits), or
+  int32_t coded;       // nonzero: lp2, alpha and beta as the linear sweeps leave them, their flags in lnp2_bwd
   const double* lp_blank;  // dense natural-log weights
   const double* lp_label;
   const double* alpha;
@@ -483,8 +497,11 @@ constexpr int kPostTileT = 8;  // frames per block
 // of alpha and beta contiguous; the tile's rows of lattice weights and of row
 // records are one contiguous range of memory each, read and completed by the
 // block.
-template <bool DENSE>
-__global__ __launch_bounds__(kPostThreads) void k2b_posteriors(PostParams p) {
+// CODED: weights and scores as the linear sweeps leave them.  Eight waves a SIMD keep two blocks
+// on a CU: the rare decoding of log2 forms had taken the registers past that (B=64 T=500 U=150:
+// 45.3 us at seven waves, 40.7 at eight).
+template <bool DENSE, bool CODED = false>
+__global__ __launch_bounds__(kPostThreads, 8) void k2b_posteriors(PostParams p) {
   const int U1 = p.U_max + 1;
   const int n_tiles = (p.T_max + kPostTileT - 1) / kPostTileT;
   const int b = static_cast<int>(blockIdx.x / n_tiles);
@@ -509,8 +526,13 @@ __global__ __launch_bounds__(kPostThreads) void k2b_posteriors(PostParams p) {
   }
   const double lnP2 = p.lnp2_fwd[b];
   const int64_t ab0 = static_cast<int64_t>(b) * (p.T_max + p.U_max + 1) * p.u_pad;
-  const LatticeRecordSrc src{p.T_max, p.U_max, p.u_pad, p.labels, p.logit_lens, p.label_lens, p.status,
-                             p.lp2,   p.alpha, p.beta,  p.lnp2_fwd};
+  LatticeRecordSrc src{p.T_max, p.U_max, p.u_pad, p.labels, p.logit_lens, p.label_lens, p.status,
+                       p.lp2,   p.alpha, p.beta,  p.lnp2_fwd, 0, 0};
+  if (CODED) {
+    const int32_t* flags = reinterpret_cast<const int32_t*>(p.lnp2_bwd + b);
+    src.log2_alpha = flags[0];
+    src.log2_beta = flags[1];
+  }
 
   const int n_items = kPostTileT * (kPostTileT - 1 + U1);
   for (int i = threadIdx.x; i < n_items; i += kPostThreads) {
@@ -524,7 +546,7 @@ __global__ __launch_bounds__(kPostThreads) void k2b_posteriors(PostParams p) {
       continue;
     }
     if (!DENSE) {
-      p.rowinfo[r] = lattice_row_record(src, b, t, u, r, T, U, lnP2);
+      p.rowinfo[r] = lattice_row_record<CODED>(src, b, t, u, r, T, U, lnP2);
       continue;
     }
     const double al = p.alpha[ab0 + static_cast<int64_t>(d) * p.u_pad + u];

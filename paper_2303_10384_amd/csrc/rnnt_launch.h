@@ -12,6 +12,7 @@
 #include "rnnt_device.h"
 #include "rnnt_k1_populate.h"
 #include "rnnt_k2_lattice.h"
+#include "rnnt_k2_linear.h"
 #include "rnnt_k3_grad.h"
 #include "rnnt_k2_viterbi.h"
 #include "rnnt_arc_kernels.h"
@@ -22,6 +23,9 @@ namespace rnnt {
 hipError_t launch_populate_lattice(rnnt_dtype_t dt, const PopulateParams& p, hipStream_t stream);
 hipError_t launch_populate_rows(rnnt_dtype_t dt, const PopulateParams& p, hipStream_t stream);
 hipError_t launch_populate_dense(rnnt_dtype_t dt, const PopulateParams& p, hipStream_t stream);
+// Whether the loss's lattices of units1 units go through the linear sweeps (and kernel 1 writes
+// their weights as probabilities): six columns of 64 units, the LDS rows of one block.
+constexpr bool linear_sweep_units(int units1) { return units1 <= 6 * kWave; }
 // kernel 2: both sweeps storing scores, the forward sweep alone, both sweeps on dense weights
 hipError_t launch_lattice_scores(int variant, const LatticeParams& p, hipStream_t stream);
 hipError_t launch_lattice_loss_only(int variant, const LatticeParams& p, hipStream_t stream);

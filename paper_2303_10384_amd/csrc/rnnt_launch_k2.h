@@ -30,6 +30,34 @@ hipError_t launch_k2_k(const LatticeParams& p, hipStream_t stream) {
 #ifndef RNNT_K2_MULTI_WAVE
 #define RNNT_K2_MULTI_WAVE 1
 #endif
+template <int NW, int VAR, int MODE>
+hipError_t launch_linear_nw(const LatticeParams& p, hipStream_t stream) {
+  const int sweeps = (MODE == kLossOnly) ? 1 : 2;
+  hipLaunchKernelGGL((k2_linear<NW, VAR, MODE>), dim3(p.B, sweeps), dim3(128 * NW), 0, stream, p);
+  return hipGetLastError();
+}
+
+template <int VAR, int MODE>
+hipError_t launch_linear_v(const LatticeParams& p, hipStream_t stream) {
+  switch ((p.U_max + kWave) / kWave) {
+    case 1: return launch_linear_nw<1, VAR, MODE>(p, stream);
+    case 2: return launch_linear_nw<2, VAR, MODE>(p, stream);
+    case 3: return launch_linear_nw<3, VAR, MODE>(p, stream);
+    case 4: return launch_linear_nw<4, VAR, MODE>(p, stream);
+    case 5: return launch_linear_nw<5, VAR, MODE>(p, stream);
+    default: return launch_linear_nw<6, VAR, MODE>(p, stream);
+  }
+}
+
+template <int MODE>
+hipError_t launch_linear(int variant, const LatticeParams& p, hipStream_t stream) {
+  switch (variant) {
+    case RNNT_VARIANT_RNNT: return launch_linear_v<0, MODE>(p, stream);
+    case RNNT_VARIANT_WRNNT: return launch_linear_v<1, MODE>(p, stream);
+    default: return launch_linear_v<2, MODE>(p, stream);
+  }
+}
+
 template <int VAR, int MODE, bool DENSE_IN>
 hipError_t launch_k2_v(const LatticeParams& p, hipStream_t stream) {
   switch (units_per_lane(p.U_max + 1)) {
@@ -103,7 +131,14 @@ template <bool DENSE>
 hipError_t launch_k2b(const PostParams& p, hipStream_t stream) {
   const int64_t blocks = static_cast<int64_t>(p.B) * ((p.T_max + kPostTileT - 1) / kPostTileT);
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((k2b_posteriors<DENSE>), dim3(static_cast<uint32_t>(blocks)), dim3(kPostThreads), 0, stream, p);
+  const dim3 grid(static_cast<uint32_t>(blocks)), block(kPostThreads);
+  if constexpr (!DENSE) {
+    if (p.coded) {
+      hipLaunchKernelGGL((k2b_posteriors<false, true>), grid, block, 0, stream, p);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k2b_posteriors<DENSE>), grid, block, 0, stream, p);
   return hipGetLastError();
 }
 

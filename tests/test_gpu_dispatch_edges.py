@@ -75,3 +75,50 @@ def test_pieces_of_rows_far_apart(torch, pkg, dtype):  # noqa: F811
     assert np.isnan(loss[0]) and not np.isnan(loss[1])
     loss_ref, grad_ref = R.rnnt_loss_grad(seen[1:], labels[1:], tl[1:], ul[1:], 0, "rnnt")
     tol_check(loss[1:], grad[1:], loss_ref, grad_ref, dtype)
+
+
+# sweeps in scaled probabilities: columns of 64 units (NW waves and their exchange, up to six; 385
+# units go to the log2 sweep), chunks of 8 diagonals (frames and units around a chunk's end), every
+# lattice, utterances that end inside an earlier column
+@pytest.mark.parametrize("variant", ["rnnt", "wrnnt", "wrnnt_allow_ignore"])
+@pytest.mark.parametrize("T,U", [(1, 0), (1, 7), (2, 1), (9, 0), (8, 1), (3, 6), (5, 4), (6, 4), (17, 63), (16, 64),
+                                 (30, 65), (25, 127), (9, 128), (40, 192), (3, 256), (12, 319), (70, 320), (11, 383),
+                                 (6, 384), (300, 9), (90, 70)])
+def test_sweep_columns_and_chunks(torch, pkg, variant, T, U):  # noqa: F811
+    for full in (True, False):
+        check(torch, pkg, 3, T, U, 6, seed=T * 1000 + U, variant=variant, full=full, sigma=2.0)
+
+
+# logits so sharp that chunks are done again with an exponent per value (weights below 2^-200, steep
+# neighbours) across columns, and -inf entries (arcs of probability 0, nodes no path reaches)
+@pytest.mark.parametrize("variant", ["rnnt", "wrnnt", "wrnnt_allow_ignore"])
+@pytest.mark.parametrize("T,U,sigma", [(30, 10, 30.0), (30, 10, 120.0), (41, 90, 60.0), (90, 140, 25.0)])
+def test_sweep_of_sharp_logits(torch, pkg, variant, T, U, sigma):  # noqa: F811
+    logits, tl, ul, labels = W.small_case(3, T, U, 7, int(T + U + sigma), sigma=1.0)
+    logits *= np.random.default_rng(T).choice([0.2, 1.0], size=logits.shape[:3] + (1,)) * sigma
+    logits = np.clip(logits, -160.0, 160.0).astype(np.float32)
+    loss, grad, seen = run_case(torch, pkg, logits, tl, ul, labels, variant=variant)
+    loss_ref, grad_ref = R.rnnt_loss_grad(seen, labels, tl, ul, 0, variant)
+    # a softmax of logits of up to 160 nats: its float32 normaliser is 2^-17 of a log2 unit off
+    assert np.all(np.abs(loss - loss_ref) <= 1e-5 * np.abs(loss_ref) + 1e-5)
+    assert np.abs(grad - grad_ref).max() <= 2e-5
+
+
+def test_sweep_of_masked_symbols(torch, pkg):  # noqa: F811
+    logits, tl, ul, labels = W.small_case(2, 20, 70, 6, 3, sigma=1.0, full=True)
+    logits[0, 3:9, 2:60, 0] = -np.inf              # no blank there: the path must climb
+    loss, grad, seen = run_case(torch, pkg, logits, tl, ul, labels)
+    with np.errstate(divide="ignore", invalid="ignore"):
+        loss_ref, grad_ref = R.rnnt_loss_grad(seen, labels, tl, ul, 0, "rnnt")
+    tol_check(loss, grad, loss_ref, grad_ref, "f32")
+
+
+def test_sweep_scales_past_the_stored_exponent(torch, pkg):  # noqa: F811
+    logits, tl, ul, labels = W.small_case(3, 12, 70, 5, 9, sigma=1.0, full=True)
+    logits[1] *= 3e6  # path probabilities below 2^-8300000: the log2 sweep of one wave
+    loss, grad, seen = run_case(torch, pkg, logits, tl, ul, labels)
+    loss_ref, grad_ref = R.rnnt_loss_grad(seen, labels, tl, ul, 0, "rnnt")
+    assert np.all(np.abs(loss - loss_ref) <= 1e-5 * np.abs(loss_ref))
+    for b in (0, 2):
+        assert np.abs(grad[b] - grad_ref[b]).max() <= 1e-5
+    assert np.all(np.isfinite(grad[1]))
