@@ -5,6 +5,7 @@ memory and the current stream.  There is no CPU fallback: if the library is
 missing or the tensors are not on a GPU, the calls raise.
 """
 import ctypes
+import functools
 import os
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -116,21 +117,32 @@ def version():
     return load_library().rnnt_version().decode()
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
+
+
+@functools.lru_cache(maxsize=None)
+def _dtype_codes():
+    torch = _torch()
+    return {torch.float32: DTYPE_F32, torch.bfloat16: DTYPE_BF16, torch.float16: DTYPE_F16}
 
 
 def dtype_code(dtype):
-    torch = _torch()
-    codes = {torch.float32: DTYPE_F32, torch.bfloat16: DTYPE_BF16, torch.float16: DTYPE_F16}
-    if dtype not in codes:
+    code = _dtype_codes().get(dtype)
+    if code is None:
         raise TypeError("logits must be float32, bfloat16 or float16, got %s" % dtype)
-    return codes[dtype]
+    return code
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _check_gpu(name, t, dtype=None):
@@ -144,7 +156,29 @@ def _check_gpu(name, t, dtype=None):
 
 def _stream_handle(device):
     torch = _torch()
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # the handle without a Stream object around it
+    if raw is not None and device.index is not None:
+        return raw(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
+
+
+# Workspace of a call whose caller passes none.  Taken from torch's allocator it is ordered on
+# the current stream, like the call's kernels, and costs a lookup; the library's own
+# hipMallocAsync went back to the driver after every synchronisation (B=16 T=400 U=300 V=32,
+# the first pass on new inputs: 824 us so, 338 us now).  None where the library refuses the shape
+# anyway, before it allocates anything.
+@functools.lru_cache(maxsize=256)
+def _workspace_size(kind, B, T_max, U_max, V):
+    if U_max + 1 > 2048 or T_max * (U_max + 1) >= 1 << 27:
+        return 0
+    return getattr(load_library(), kind)(Shape(B, T_max, U_max, V, DTYPE_F32, DTYPE_F32))
+
+
+def _call_workspace(nbytes, device):
+    if not 0 < nbytes < 1 << 42:
+        return None
+    torch = _torch()
+    return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
 def shape_of(logits, grad_dtype=None):
@@ -155,6 +189,12 @@ def shape_of(logits, grad_dtype=None):
 
 def loss_workspace_bytes(B, T_max, U_max, V, dtype_code_=DTYPE_F32):
     return load_library().rnnt_loss_workspace_bytes(Shape(B, T_max, U_max, V, dtype_code_, dtype_code_))
+
+
+def _workspace_args(workspace):
+    if workspace is None:
+        return None, 0
+    return workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 
 def _check_loss_inputs(logits, labels, logit_lens, label_lens, variant, grad_dtype=None):
@@ -182,12 +222,13 @@ def step_forward(logits, labels, logit_lens, label_lens, blank, variant):
     shape = _check_loss_inputs(logits, labels, logit_lens, label_lens, variant)
     dev = logits.device
     loss = torch.empty(shape.B, dtype=torch.float32, device=dev)
-    rows = torch.empty((logits.numel() // shape.V, 4), dtype=torch.int32, device=dev)
+    rows = torch.empty((shape.B * shape.T_max * (shape.U_max + 1), 4), dtype=torch.int32, device=dev)
     # from torch's allocator, ordered on the current stream like the kernels that use it
-    workspace = torch.empty(lib.rnnt_step_workspace_bytes(shape), dtype=torch.uint8, device=dev)
+    workspace = _call_workspace(_workspace_size("rnnt_step_workspace_bytes", shape.B, shape.T_max, shape.U_max,
+                                                shape.V), dev)
+    ws_ptr, ws_bytes = _workspace_args(workspace)
     st = lib.rnnt_step_forward(_ptr(logits), shape, _ptr(labels), _ptr(logit_lens), _ptr(label_lens), int(blank),
-                               VARIANTS[variant], _ptr(loss), _ptr(rows), _ptr(workspace), workspace.numel(),
-                               _stream_handle(dev))
+                               VARIANTS[variant], _ptr(loss), _ptr(rows), ws_ptr, ws_bytes, _stream_handle(dev))
     if st != RNNT_OK:
         raise RNNTError(st, "rnnt_loss")
     return loss, rows
@@ -225,19 +266,9 @@ def rnnt_loss(logits, labels, logit_lens, label_lens, blank=0, variant="rnnt", n
     """
     torch = _torch()
     lib = load_library()
-    _check_gpu("logits", logits)
-    _check_gpu("labels", labels, torch.int32)
-    _check_gpu("logit_lens", logit_lens, torch.int32)
-    _check_gpu("label_lens", label_lens, torch.int32)
-    if logits.dim() != 4:
-        raise ValueError("logits must be (B, T_max, U_max+1, V)")
     if grad_out is not None and grad_dtype is None:
         grad_dtype = grad_out.dtype
-    shape = shape_of(logits, grad_dtype)
-    if labels.shape != (shape.B, shape.U_max) or logit_lens.shape != (shape.B,) or label_lens.shape != (shape.B,):
-        raise ValueError("labels must be (B, U_max) and the length vectors (B,)")
-    if variant not in VARIANTS:
-        raise ValueError("variant must be one of %s" % sorted(VARIANTS))
+    shape = _check_loss_inputs(logits, labels, logit_lens, label_lens, variant, grad_dtype)
     dev = logits.device
     loss = loss_out if loss_out is not None else torch.empty(shape.B, dtype=torch.float32, device=dev)
     _check_gpu("loss_out", loss, torch.float32)
@@ -248,10 +279,12 @@ def rnnt_loss(logits, labels, logit_lens, label_lens, blank=0, variant="rnnt", n
         _check_gpu("grad_out", grad, gdt)
         if grad.shape != logits.shape:
             raise ValueError("grad_out must have the logits' shape")
-    ws_ptr, ws_bytes = ctypes.c_void_p(0), 0
     if workspace is not None:
         _check_gpu("workspace", workspace)
-        ws_ptr, ws_bytes = _ptr(workspace), workspace.numel() * workspace.element_size()
+    else:
+        workspace = _call_workspace(_workspace_size("rnnt_loss_workspace_bytes", shape.B, shape.T_max, shape.U_max,
+                                                    shape.V), dev)
+    ws_ptr, ws_bytes = _workspace_args(workspace)
     if events is None:
         st = lib.rnnt_loss(_ptr(logits), shape, _ptr(labels), _ptr(logit_lens), _ptr(label_lens), int(blank),
                            VARIANTS[variant], _ptr(loss), _ptr(grad), ws_ptr, ws_bytes, _stream_handle(dev))
@@ -333,7 +366,7 @@ def lattice_scores(lp_blank, lp_label, logit_lens, label_lens, variant="rnnt"):
     st = lib.rnnt_lattice_scores(_ptr(lp_blank), _ptr(lp_label), shape, _ptr(logit_lens), _ptr(label_lens),
                                  VARIANTS[variant], _ptr(out["alpha"]), _ptr(out["beta"]), _ptr(out["loss"]),
                                  _ptr(out["loss_bwd"]), _ptr(out["occ_blank"]), _ptr(out["occ_label"]),
-                                 ctypes.c_void_p(0), 0, _stream_handle(dev))
+                                 None, 0, _stream_handle(dev))
     if st != RNNT_OK:
         raise RNNTError(st, "rnnt_lattice_scores")
     return out
@@ -355,17 +388,7 @@ def viterbi_align(logits, labels, logit_lens, label_lens, blank=0, variant="rnnt
     """
     torch = _torch()
     lib = load_library()
-    _check_gpu("logits", logits)
-    _check_gpu("labels", labels, torch.int32)
-    _check_gpu("logit_lens", logit_lens, torch.int32)
-    _check_gpu("label_lens", label_lens, torch.int32)
-    if logits.dim() != 4:
-        raise ValueError("logits must be (B, T_max, U_max+1, V)")
-    shape = shape_of(logits)
-    if labels.shape != (shape.B, shape.U_max) or logit_lens.shape != (shape.B,) or label_lens.shape != (shape.B,):
-        raise ValueError("labels must be (B, U_max) and the length vectors (B,)")
-    if variant not in VARIANTS:
-        raise ValueError("variant must be one of %s" % sorted(VARIANTS))
+    shape = _check_loss_inputs(logits, labels, logit_lens, label_lens, variant)
     dev = logits.device
     if outputs is None:
         score = torch.empty(shape.B, dtype=torch.float32, device=dev)
@@ -378,10 +401,12 @@ def viterbi_align(logits, labels, logit_lens, label_lens, blank=0, variant="rnnt
         _check_gpu("span", span, torch.int32)
         if score.shape != (shape.B,) or frames.shape != (shape.B, shape.U_max) or span.shape != (shape.B, 2):
             raise ValueError("outputs must be (B,), (B, U_max) and (B, 2)")
-    ws_ptr, ws_bytes = ctypes.c_void_p(0), 0
     if workspace is not None:
         _check_gpu("workspace", workspace)
-        ws_ptr, ws_bytes = _ptr(workspace), workspace.numel() * workspace.element_size()
+    else:
+        workspace = _call_workspace(_workspace_size("rnnt_viterbi_workspace_bytes", shape.B, shape.T_max, shape.U_max,
+                                                    shape.V), dev)
+    ws_ptr, ws_bytes = _workspace_args(workspace)
     args = (_ptr(logits), shape, _ptr(labels), _ptr(logit_lens), _ptr(label_lens), int(blank), VARIANTS[variant],
             _ptr(score), _ptr(frames), _ptr(span), ws_ptr, ws_bytes, _stream_handle(dev))
     st = lib.rnnt_viterbi(*args) if events is None else lib.rnnt_viterbi_timed(*args, events)
@@ -476,10 +501,11 @@ def arc_loss(logits, logit_lens, label_lens, plan, need_grad=True, workspace=Non
         _check_gpu("grad_out", grad, gdt)
         if grad.shape != logits.shape:
             raise ValueError("grad_out must have the logits' shape")
-    ws_ptr, ws_bytes = ctypes.c_void_p(0), 0
     if workspace is not None:
         _check_gpu("workspace", workspace)
-        ws_ptr, ws_bytes = _ptr(workspace), workspace.numel() * workspace.element_size()
+    elif (plan.desc.B, plan.desc.T_max, plan.desc.U_max, plan.desc.V) == (shape.B, shape.T_max, shape.U_max, shape.V):
+        workspace = _call_workspace(arc_loss_workspace_bytes(plan), dev)
+    ws_ptr, ws_bytes = _workspace_args(workspace)
     args = (_ptr(logits), shape, _ptr(logit_lens), _ptr(label_lens), ctypes.byref(plan.desc), _ptr(plan.image),
             _ptr(loss), _ptr(grad), ws_ptr, ws_bytes, _stream_handle(dev))
     st = lib.rnnt_arc_loss(*args) if events is None else lib.rnnt_arc_loss_timed(*args, events)

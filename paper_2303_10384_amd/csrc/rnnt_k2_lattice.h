@@ -60,7 +60,7 @@ enum LatticeMode : int {
 enum WeightForm : int {
   kWeightsLog2 = 0,   // kernel 1's lattice form in log2 units
   kWeightsDense = 1,  // dense natural-log arrays (the lattice-only entry point)
-  kWeightsCoded = 2,  // kernel 1's lattice form as probabilities (coded_weight)
+  kWeightsCoded = 2,  // kernel 1's lattice form as probabilities (code_weight)
 };
 
 struct LatticeParams {
