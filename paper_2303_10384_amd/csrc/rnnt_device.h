@@ -129,7 +129,7 @@ __device__ __forceinline__ RowInfo lattice_row_record(const LatticeRecordSrc& s,
   o.lse2 = lse2;
   if (CODED && !(s.log2_alpha | s.log2_beta) && lnP2 > 0.5 * kNoArc && !(w.x < 0.0) && !(w.y < 0.0)) {
     // scores m * 2^E, weights as probabilities: the product of three numbers (scores within
-    // [2^-320, 2^450] and probabilities from 2^-200, so it neither over- nor underflows) times a
+    // [2^-410, 2^450] and probabilities from 2^-200, so it neither over- nor underflows) times a
     // power of two
     const double eP = __builtin_rint(lnP2);
     const float fP = fast_exp2(static_cast<float>(eP - lnP2));  // 2^(eP) / P

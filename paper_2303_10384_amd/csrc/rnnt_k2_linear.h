@@ -32,9 +32,13 @@
 // exponent of its own for every value (SLOW: no range limit, about ten times slower a step).
 // What a kept sweep loses to underflow in a chunk is below 2^-1022 in some lane's scale,
 // reaches another lane's scale multiplied by at most 2^kMaxRise, and valid scores there are
-// at least 2^-kMinExp: 2^-40 of any of them.  On N(0, 3^2) logits the rise over 7 lanes stays
-// under 300 and a score falls by under 160 in a chunk; with sharp alignments added (8 nats,
-// V = 29) the rise stays under 600.
+// at least 2^-kMinExp: 2^-40 of any of them.  A score's fall (from the middle of a chunk to the end
+// of the next) is largest where the first chunks climb the labels of frame 0: under 170 on N(0, 3^2)
+// logits, 240 with an alignment's symbols raised by 8 nats, 250 by 12, 320 by 16 and 390 by 20 (N(0,
+// 2^2)); the rise over 7 lanes stays under 360 in all of them.  So one column has its limits at 410
+// and 572 (at 320 and 662, B=4 T=500 U=20 V=64 raised by 20 nats took 200 us a call, not 50).  Across
+// columns the rise is taken over up to 14 lanes, and the limits lie at 320 and 662 (at 410 and 572,
+// B=8 T=300 U=200 V=64 raised by 12 nats took 296 us, not 105).
 //
 // Scores are stored by diagonal as before, 8 bytes a node: m with its low 24 mantissa bits
 // replaced by E (28 bits of m stay: 4e-9 relative, against the ~1e-7 of the float32
@@ -55,10 +59,11 @@ constexpr int kTileRing = 24;      // LDS rows (diagonals) per column of 64 unit
 constexpr int kTilesAhead = 4;     // chunks of weights in flight in a loader's registers
 constexpr int kScaleStep = 4;      // the next chunk's scales are set after this many steps
 constexpr int kWaveLag = 2;        // chunks between a wave and the neighbour it takes values from
-constexpr int kMinExp = 320;
+template <int NW>
+constexpr int kMinExp = NW == 1 ? 410 : 320;
 constexpr int kMaxExp = 450;  // with kMinExp and the weights' 2^-200: products of two scores and a weight are normal
-constexpr int kMaxRise = 662;
-static_assert(1022 - kMaxRise - kMinExp >= 40, "lost terms must stay below the kept ones");
+template <int NW>
+constexpr int kMaxRise = 1022 - 40 - kMinExp<NW>;  // lost terms stay below the kept ones
 constexpr int kMaxScale = (1 << 23) - 4096;  // |E| of a stored score
 constexpr int kNoScale = -(1 << 30);
 constexpr int kLowest = static_cast<int>(0x80000000u);
@@ -312,8 +317,9 @@ __device__ __forceinline__ int linear_sweep(const LatticeParams& p, LinearShared
     double ratio = 1.0;      // 2^(the neighbour's scale - this lane's), of the chunk
     double x_in[kChunk];     // the neighbour's values for the chunk (NW > 1)
     int rise_in = kNoScale;  // its largest scale near the edge
-    // a lane above U holds no node and its scale no meaning
-    const int rise_limit = u <= U ? kMaxRise : 0x3fffffff;
+    // a lane above U holds no node and its scale no meaning; less kNoScale the limit stays below 2^31
+    // (at 2^30 - 1 a scale above 1, as W-Transducer scores reach, wrapped and sent the sweep to SLOW)
+    const int rise_limit = u <= U ? kMaxRise<NW> : 1 << 29;
     auto read_in = [&](int g, double (&x)[kChunk], int& e, int& rise) {
 #pragma unroll
       for (int s = 0; s < kChunk; ++s) x[s] = sh.xch[in_slot][g & 3][s];
@@ -326,7 +332,7 @@ __device__ __forceinline__ int linear_sweep(const LatticeParams& p, LinearShared
       const int out = (u - (d - (T - 1))) | (min(d, U) - u);
       int ex = __builtin_amdgcn_frexp_exp(x);
       ex = __builtin_amdgcn_class(x, 0x100) ? ex : -100000;
-      worst |= ((ex + kMinExp) | (kMaxExp - ex)) & ~out;
+      worst |= ((ex + kMinExp<NW>) | (kMaxExp - ex)) & ~out;
     };
     auto fast_chunk = [&](int g, const double2 (&w)[kChunk], double2 (&w_next)[kChunk], auto whole_tag) {
       constexpr bool whole = decltype(whole_tag)::value;

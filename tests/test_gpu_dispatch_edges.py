@@ -104,6 +104,25 @@ def test_sweep_of_sharp_logits(torch, pkg, variant, T, U, sigma):  # noqa: F811
     assert np.abs(grad - grad_ref).max() <= 2e-5
 
 
+# an alignment's symbols raised by up to 20 nats (the falls and rises the one-sweep form is sized for, on
+# both sides of its limits), utterances of fewer units than the padded shape: lanes without a node
+@pytest.mark.parametrize("variant", ["rnnt", "wrnnt", "wrnnt_allow_ignore"])
+@pytest.mark.parametrize("T,U,peak", [(60, 10, 8.0), (90, 20, 20.0), (70, 63, 12.0), (60, 110, 12.0), (40, 140, 20.0)])
+def test_sweep_of_peaked_logits(torch, pkg, variant, T, U, peak):  # noqa: F811
+    logits, tl, ul, labels = W.small_case(3, T, U, 29, T + U, sigma=2.0)
+    rng = np.random.default_rng(U)
+    for b in range(3):
+        frame = np.append(np.sort(rng.integers(0, tl[b], size=ul[b])), 1 << 30)
+        sym = np.where(np.arange(T)[:, None] >= frame, np.append(labels[b, :ul[b]], 0), 0)
+        np.put_along_axis(logits[b, :, :ul[b] + 1], sym[..., None],
+                          np.take_along_axis(logits[b, :, :ul[b] + 1], sym[..., None], 2) + np.float32(peak), 2)
+    loss, grad, seen = run_case(torch, pkg, logits, tl, ul, labels, variant=variant)
+    loss_ref, grad_ref = R.rnnt_loss_grad(seen, labels, tl, ul, 0, variant)
+    # a loss is a sum of T + U weights, each off by its float32 normaliser's last bit (6e-8 of up to 32 nats)
+    assert np.all(np.abs(loss - loss_ref) <= 1e-5 * np.abs(loss_ref) + 2e-6 * (T + U))
+    assert np.abs(grad - grad_ref).max() <= 2e-5
+
+
 def test_sweep_of_masked_symbols(torch, pkg):  # noqa: F811
     logits, tl, ul, labels = W.small_case(2, 20, 70, 6, 3, sigma=1.0, full=True)
     logits[0, 3:9, 2:60, 0] = -np.inf              # no blank there: the path must climb
