@@ -50,7 +50,7 @@ KERNEL_SOURCES = SOURCES["loss"]
 KERNEL_SETS = {  # short name -> substring of the demangled kernel name
     "loss": {
         "k1_populate": "rnnt::k1_populate",
-        "k2_lattice": "rnnt::k2_lattice",
+        "k2_lattice": "rnnt::k2_l",  # k2_linear up to 384 units, k2_lattice past them
         "k2b_posteriors": "rnnt::k2b_posteriors",
         "k3_grad": "rnnt::k3_grad",
     },
