@@ -287,7 +287,7 @@ rnnt_status_t run_rows(const void* logits, const rnnt_shape_t& shape, const int3
   p1.n_elem = n_elem;
   p1.lp2 = reinterpret_cast<double2*>(ws + L.lp2);
   p1.keep_logits = keep;
-  p1.linear = linear_sweep_units(shape.U_max + 1);
+  p1.linear = linear_sweep_units(shape.T_max, shape.U_max);
   p1.pack_lse2f = 1;  // the posterior kernel reads lse2f from the weights
   if (launch_populate_lattice(shape.dtype, p1, stream) != hipSuccess) return RNNT_ERR_HIP;
   if (mark(1) != hipSuccess) return RNNT_ERR_HIP;

@@ -5,7 +5,7 @@
 namespace rnnt {
 
 hipError_t launch_lattice_scores(int variant, const LatticeParams& p, hipStream_t stream) {
-  return linear_sweep_units(p.U_max + 1) ? k2::launch_linear<kScores>(variant, p, stream)
+  return linear_sweep_units(p.T_max, p.U_max) ? k2::launch_linear<kScores>(variant, p, stream)
                                          : k2::launch_k2<kScores, false>(variant, p, stream);
 }
 
