@@ -128,20 +128,25 @@ __device__ __forceinline__ RowInfo lattice_row_record(const LatticeRecordSrc& s,
   RowInfo o;
   o.lse2 = lse2;
   if (CODED && !(s.log2_alpha | s.log2_beta) && lnP2 > 0.5 * kNoArc && !(w.x < 0.0) && !(w.y < 0.0)) {
-    // scores m * 2^E, weights as probabilities: the product of three numbers (scores within
-    // [2^-410, 2^450] and probabilities from 2^-200, so it neither over- nor underflows) times a
-    // power of two
+    // scores m * 2^E, weights as probabilities: the product of the three mantissas, all in [0.5, 1),
+    // times a power of two from the exponents.  The sweeps bound a score only at the end of a chunk of
+    // diagonals; inside one its m may lie hundreds of binary orders below, where the product of the
+    // three numbers as they are would underflow (alpha 2^-482, weight 2^-23, beta 2^-593 of a posterior of 0.4)
     const double eP = __builtin_rint(lnP2);
     const float fP = fast_exp2(static_cast<float>(eP - lnP2));  // 2^(eP) / P
-    const int e0 = score_exp(al) - static_cast<int>(eP);
+    auto mant = [](double x) { return __builtin_amdgcn_frexp_mant(x); };
+    auto expo = [](double x) { return __builtin_amdgcn_frexp_exp(x); };
+    const double am = mant(al);
+    const int e0 = expo(al) + score_exp(al) - static_cast<int>(eP);
     auto posterior = [&](double m, int e) {  // 0 below 2^-126, like the exponential unit
       const float x = static_cast<float>(ldexp(m, e)) * fP;
       return x < 0x1p-126f ? 0.f : x;
     };
-    const double down = closing ? 1.0 : b_down;
-    const int e_down = closing ? 0 : score_exp(b_down);
-    o.occ_blank = has_blank ? posterior(al * w.x * down, e0 + e_down) : 0.f;
-    o.occ_label = has_label ? posterior(al * w.y * b_right, e0 + score_exp(b_right)) : 0.f;
+    const double dm = closing ? 1.0 : mant(b_down);
+    const int e_down = closing ? 0 : expo(b_down) + score_exp(b_down);
+    o.occ_blank = has_blank ? posterior(am * mant(w.x) * dm, e0 + expo(w.x) + e_down) : 0.f;
+    o.occ_label =
+        has_label ? posterior(am * mant(w.y) * mant(b_right), e0 + expo(w.y) + expo(b_right) + score_exp(b_right)) : 0.f;
   } else {
     double la = al, ld = b_down, lr = b_right, wx = w.x, wy = w.y;
     if (CODED) {

@@ -1,0 +1,70 @@
+"""The loss's sweep in scaled probabilities on networks far sharper than trained ones: weights of
+2^-20 to 2^-199 on the best paths, where a score falls and is refilled within a few diagonals.
+Against the float64 oracle with the bounds of test_gpu_parity: gradient 1e-5 absolute; loss 1e-5
+relative, plus 6e-8 for each of the T + U weights of a path, whose float32 normalisers are that far
+off (some losses here are next to 0, and the wild-card arcs even make them negative)."""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import rnnt_ref as R
+from test_gpu_parity import pkg, run_case, torch  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def announce(request):
+    sys.__stderr__.write("\n[gpu-test] %s\n" % request.node.nodeid)
+    sys.__stderr__.flush()
+    yield
+
+
+def logits_of(x, y):
+    """Logits of three symbols (blank 0, label 1, the rest) with p(blank) = 2^-x, p(label) = 2^-y."""
+    pb, pl = 2.0 ** -np.asarray(x, float), 2.0 ** -np.asarray(y, float)
+    rest = 1.0 - pb - pl
+    return np.stack([np.log(pb), np.log(pl), np.where(rest > 0, np.log(np.where(rest > 0, rest, 1.0)), -200.0)],
+                    axis=-1).astype(np.float32)
+
+
+def check(torch, pkg, logits, tl, ul, variant="rnnt"):  # noqa: F811
+    labels = np.ones((logits.shape[0], logits.shape[2] - 1), np.int32)
+    tl, ul = np.asarray(tl, np.int32), np.asarray(ul, np.int32)
+    loss, grad, seen = run_case(torch, pkg, logits, tl, ul, labels, variant=variant)
+    loss_ref, grad_ref = R.rnnt_loss_grad(seen, labels, tl, ul, 0, variant)
+    assert np.all(np.abs(loss - loss_ref) <= 1e-5 * np.abs(loss_ref) + 6e-8 * (tl + ul + 1)), (loss, loss_ref)
+    assert np.abs(grad - grad_ref).max() <= 1e-5
+
+
+# (x, y) of 24 frames of 5 nodes: p(blank) = 2^-x, p(label) = 2^-y.  The label posterior of node
+# (12, 1) is 0.40, the product of alpha 2^-482, weight 2^-23 and beta 2^-593 of their lanes' scales
+REFILLED = """
+    1,100 1,199 1,1 1,199 1,1 | 1,199 1,199 1,1 1,1 1,1 | 100,1 1,199 1,199 1,1 1,1 | 50,1 199,141 199,199 1,1 1,1 |
+    50,1 1,199 1,1 1,1 199,1 | 41,1 199,199 1,1 199,199 1,1 | 41,199 1,1 199,140 1,1 1,1 |
+    41,199 199,199 199,1 199,1 91,1 | 41,199 1,199 1,1 199,1 100,1 | 41,199 1,199 1,1 1,1 41,1 |
+    1,199 199,199 1,1 199,1 50,1 | 1,199 1,1 1,199 1,1 1,1 | 1,199 1,1 1,1 1,199 20,1 | 1,1 1,199 1,1 1,199 21,1 |
+    50,1 1,1 199,199 199,199 1,1 | 100,1 199,199 1,199 1,199 1,1 | 1,1 199,1 199,199 1,199 21,1 |
+    100,199 1,1 1,1 1,199 41,1 | 100,199 1,1 199,1 199,199 21,1 | 100,1 199,50 100,199 1,1 1,1 |
+    199,1 100,199 199,1 199,1 100,1 | 1,1 1,199 1,1 1,1 50,1 | 1,1 1,199 1,1 1,1 50,1 | 1,1 1,199 1,199 1,1 1,1"""
+
+
+def test_score_refilled_inside_a_chunk(torch, pkg):  # noqa: F811
+    cells = np.array([[tuple(map(int, c.split(","))) for c in row.split()] for row in REFILLED.split("|")])
+    check(torch, pkg, logits_of(cells[..., 0], cells[..., 1])[None], [24], [4])
+
+
+# lattices drawn from a few steep weights, so that most nodes lie hundreds of binary orders off the
+# best path and the best path itself takes unlikely arcs
+@pytest.mark.parametrize("variant", ["rnnt", "wrnnt", "wrnnt_allow_ignore"])
+@pytest.mark.parametrize("seed", range(8))
+def test_steep_random_lattices(torch, pkg, variant, seed):  # noqa: F811
+    rng = np.random.default_rng(700 + seed)
+    T, U, B = int(rng.integers(9, 40)), int(rng.integers(1, 9)), 12
+    steep = [1, 1, 1, 20, 50, 100, 199][: int(rng.integers(4, 8))]
+    x = rng.choice(steep, size=(B, T, U + 1))
+    y = rng.choice(steep, size=(B, T, U + 1))
+    tl = rng.integers(max(1, T // 2), T, size=B, endpoint=True)
+    ul = rng.integers(0, U, size=B, endpoint=True)
+    check(torch, pkg, logits_of(x, y), tl, ul, variant)
