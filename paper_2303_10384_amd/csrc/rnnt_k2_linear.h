@@ -224,6 +224,9 @@ __device__ __forceinline__ int linear_sweep(const LatticeParams& p, LinearShared
     const __amdgpu_buffer_rsrc_t s_rsrc = make_buffer(scores, static_cast<int64_t>(ND + 1) * p.u_pad * 8);
     const int row_bytes = p.u_pad * 8;
     const Scaled w_close = scaled_weight(w_utt[static_cast<int64_t>(T - 1) * U1 + U].x);
+    // a closing blank below the scales' range (its logit masked with a finite number, -1e30): the clamp of
+    // scaled_weight would be the loss, and the first score has no exponent to be stored with
+    if (w_close.m != 0.0 && w_close.e < -kMaxScale) bad = 1;
     const bool first_lane = fwd ? u == 0 : u == U;  // the node the sweep starts from
     const Scaled start = fwd ? Scaled{1.0, 0} : scaled_norm(w_close);
     double m = first_lane ? start.m : 0.0;

@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 from oracle import rnnt_ref as R
-from test_gpu_parity import pkg, run_case, torch  # noqa: F401  (fixtures)
+from test_gpu_parity import pkg, run_case, tol_check, torch  # noqa: F401  (fixtures)
 
 pytestmark = pytest.mark.gpu
 
@@ -68,3 +68,18 @@ def test_steep_random_lattices(torch, pkg, variant, seed):  # noqa: F811
     tl = rng.integers(max(1, T // 2), T, size=B, endpoint=True)
     ul = rng.integers(0, U, size=B, endpoint=True)
     check(torch, pkg, logits_of(x, y), tl, ul, variant)
+
+
+# the closing blank masked with a finite number, down to float32's lowest: the loss is that number where
+# every path takes the arc, and untouched where paths may leave it out (allow-ignore, T > 1)
+@pytest.mark.parametrize("variant", ["rnnt", "wrnnt", "wrnnt_allow_ignore"])
+@pytest.mark.parametrize("T,U", [(1, 0), (3, 2), (9, 3), (17, 0)])
+def test_masked_closing_blank(torch, pkg, variant, T, U):  # noqa: F811
+    masks = [-1e4, -1e6, -1e10, -1e30, float(np.finfo(np.float32).min)]
+    logits = np.random.default_rng(T).normal(size=(len(masks), T, U + 1, 5)).astype(np.float32)
+    logits[:, T - 1, U, 0] = masks
+    labels = np.ones((len(masks), U), np.int32)
+    tl, ul = np.full(len(masks), T, np.int32), np.full(len(masks), U, np.int32)
+    loss, grad, seen = run_case(torch, pkg, logits, tl, ul, labels, variant=variant)
+    loss_ref, grad_ref = R.rnnt_loss_grad(seen, labels, tl, ul, 0, variant)
+    tol_check(loss, grad, loss_ref, grad_ref, "f32", tl, ul)
