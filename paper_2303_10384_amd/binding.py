@@ -95,6 +95,8 @@ def load_library():
     lib.rnnt_arc_loss_timed.argtypes = [vp, Shape, vp, vp, ctypes.POINTER(ArcPlanDesc), vp, vp, vp, vp, sz, vp, vp]
     lib.rnnt_arc_loss_timed.restype = ctypes.c_int
     # csrc/rnnt_step.h: the autograd wrapper's two calls
+    lib.rnnt_scaled_sweep_columns.argtypes = [i32]
+    lib.rnnt_scaled_sweep_columns.restype = i32
     lib.rnnt_step_workspace_bytes.argtypes = [Shape]
     lib.rnnt_step_workspace_bytes.restype = sz
     lib.rnnt_step_forward.argtypes = [vp, Shape, vp, vp, vp, i32, ctypes.c_int, vp, vp, vp, sz, vp]

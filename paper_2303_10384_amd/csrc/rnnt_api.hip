@@ -287,7 +287,7 @@ rnnt_status_t run_rows(const void* logits, const rnnt_shape_t& shape, const int3
   p1.n_elem = n_elem;
   p1.lp2 = reinterpret_cast<double2*>(ws + L.lp2);
   p1.keep_logits = keep;
-  p1.linear = linear_sweep_units(shape.T_max, shape.U_max);
+  p1.linear = scaled_sweep_columns(shape.U_max) != 0;
   p1.pack_lse2f = 1;  // the posterior kernel reads lse2f from the weights
   if (launch_populate_lattice(shape.dtype, p1, stream) != hipSuccess) return RNNT_ERR_HIP;
   if (mark(1) != hipSuccess) return RNNT_ERR_HIP;
@@ -428,6 +428,8 @@ rnnt_status_t rnnt_loss(const void* logits, rnnt_shape_t shape, const int32_t* l
   return rnnt_loss_timed(logits, shape, labels, logit_lens, label_lens, blank, variant, loss_out, grad_out,
                          workspace, workspace_bytes, stream, nullptr);
 }
+
+int32_t rnnt_scaled_sweep_columns(int32_t U_max) { return scaled_sweep_columns(U_max); }
 
 size_t rnnt_step_workspace_bytes(rnnt_shape_t shape) {
   if (check_shape(shape) != RNNT_OK) return 0;

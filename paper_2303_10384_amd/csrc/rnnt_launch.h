@@ -23,16 +23,12 @@ namespace rnnt {
 hipError_t launch_populate_lattice(rnnt_dtype_t dt, const PopulateParams& p, hipStream_t stream);
 hipError_t launch_populate_rows(rnnt_dtype_t dt, const PopulateParams& p, hipStream_t stream);
 hipError_t launch_populate_dense(rnnt_dtype_t dt, const PopulateParams& p, hipStream_t stream);
-// Whether the loss's lattices of units1 units go through the linear sweeps (and kernel 1 writes
-// their weights as probabilities): six columns of 64 units, the LDS rows of one block.
-// Over several columns only while the units are at most 7/8 of the frames: with as many units as frames
-// the label arcs are climbed without a blank between, the scores of neighbouring units lie up to 50 binary
-// orders apart (T=60 U=110, symbols raised by 8 nats: 355 over 7 units), and over the 14 lanes compared
-// across columns that leaves the scaled sweep's limits, which then costs two sweeps.  The line
-// at 7/8 is from these rises, worked out on the CPU; the two forms were not timed around it.
-constexpr bool linear_sweep_units(int T_max, int U_max) {
-  return U_max < kWave || (U_max < 6 * kWave && 8 * static_cast<int64_t>(U_max) <= 7 * static_cast<int64_t>(T_max));
-}
+// Columns of 64 units of the scaled sweep that takes the loss's lattices (kernel 1 then writes their weights
+// as probabilities), or 0: the log2 sweep takes them.  Six columns' LDS rows fill a CU; the choice depends on
+// nothing else, so a lattice's result does not depend on the frames it is padded to.  (Lattices of more than
+// 7/8 as many units as frames had been kept from the scaled sweep: a loss of -3.4e-4, T=2 U=0 padded to T=11
+// U=383 under the allow-ignore arcs, then came out 1.4e-4 off, 4.7e-8 being what the log2 sweep rounds by.)
+constexpr int scaled_sweep_columns(int U_max) { return U_max < 6 * kWave ? (U_max + kWave) / kWave : 0; }
 // kernel 2: both sweeps storing scores, the forward sweep alone, both sweeps on dense weights
 hipError_t launch_lattice_scores(int variant, const LatticeParams& p, hipStream_t stream);
 hipError_t launch_lattice_loss_only(int variant, const LatticeParams& p, hipStream_t stream);

@@ -39,7 +39,7 @@ hipError_t launch_linear_nw(const LatticeParams& p, hipStream_t stream) {
 
 template <int VAR, int MODE>
 hipError_t launch_linear_v(const LatticeParams& p, hipStream_t stream) {
-  switch ((p.U_max + kWave) / kWave) {
+  switch (scaled_sweep_columns(p.U_max)) {
     case 1: return launch_linear_nw<1, VAR, MODE>(p, stream);
     case 2: return launch_linear_nw<2, VAR, MODE>(p, stream);
     case 3: return launch_linear_nw<3, VAR, MODE>(p, stream);

@@ -4,8 +4,8 @@
 namespace rnnt {
 
 hipError_t launch_lattice_loss_only(int variant, const LatticeParams& p, hipStream_t stream) {
-  return linear_sweep_units(p.T_max, p.U_max) ? k2::launch_linear<kLossOnly>(variant, p, stream)
-                                         : k2::launch_k2<kLossOnly, false>(variant, p, stream);
+  return scaled_sweep_columns(p.U_max) ? k2::launch_linear<kLossOnly>(variant, p, stream)
+                                       : k2::launch_k2<kLossOnly, false>(variant, p, stream);
 }
 
 }  // namespace rnnt

@@ -5,8 +5,8 @@
 namespace rnnt {
 
 hipError_t launch_lattice_scores(int variant, const LatticeParams& p, hipStream_t stream) {
-  return linear_sweep_units(p.T_max, p.U_max) ? k2::launch_linear<kScores>(variant, p, stream)
-                                         : k2::launch_k2<kScores, false>(variant, p, stream);
+  return scaled_sweep_columns(p.U_max) ? k2::launch_linear<kScores>(variant, p, stream)
+                                       : k2::launch_k2<kScores, false>(variant, p, stream);
 }
 
 hipError_t launch_posteriors_rows(const PostParams& p, hipStream_t stream) { return k2::launch_k2b<false>(p, stream); }

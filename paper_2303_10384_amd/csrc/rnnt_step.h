@@ -12,6 +12,10 @@ extern "C" {
 // Bytes of workspace of rnnt_step_forward (0 for an invalid shape).
 size_t rnnt_step_workspace_bytes(rnnt_shape_t shape);
 
+// Columns of 64 units of the scaled sweep that the loss takes lattices of up to U_max units through, 0 for
+// the log2 sweep (for tests of what a shape reaches).
+int32_t rnnt_scaled_sweep_columns(int32_t U_max);
+
 // Losses, and in rows_out the row records: 16 bytes for each of the B * T_max * (U_max+1)
 // logits rows, 16-byte aligned.  workspace: 256-byte aligned, free again after the call's work.
 rnnt_status_t rnnt_step_forward(const void* logits, rnnt_shape_t shape, const int32_t* labels,

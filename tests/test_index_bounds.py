@@ -423,3 +423,12 @@ def test_viterbi_walk_by_label_moves(var, T, U, density):
         dec = rng.random((ND + 65, U + 1)) < density
         for t_end in {T - 1, max(0, T // 2)}:
             assert _walk_by_label_moves(dec, t_end, U, var, ND) == _walk_by_diagonal(dec, t_end, U, var)
+
+
+@pytest.mark.parametrize("U_max,columns", [(0, 1), (63, 1), (64, 2), (127, 2), (128, 3), (192, 4), (255, 4), (256, 5),
+                                           (319, 5), (320, 6), (383, 6), (384, 0), (2047, 0)])
+def test_columns_of_the_scaled_sweep(U_max, columns):
+    """Which sweep a lattice takes depends on its padded units alone: the GPU tests' shapes of up to 383 units
+    reach one to six columns of the scaled sweep whatever their frames."""
+    import paper_2303_10384_amd as P
+    assert P.load_library().rnnt_scaled_sweep_columns(U_max) == columns
