@@ -57,8 +57,9 @@ struct LatticeRecordSrc {
   const int32_t* logit_lens;    // (B)
   const int32_t* label_lens;    // (B)
   const int32_t* status;        // (B) 0: good utterance
-  const double2* lp2;           // (B, T_max, U_max+1) {lp_blank, lp_label} * log2 e, lse2f in their low bits
-  const double* alpha;          // (B, T_max+U_max+1, u_pad) by diagonal, log2 units
+  const double2* lp2;           // (B, T_max, U_max+1) {lp_blank, lp_label} * log2 e (scaled sweep: code_weight), lse2f in
+                                // their low bits
+  const double* alpha;          // (B, T_max+U_max+1, u_pad) by diagonal, log2 units (scaled sweep: m and E)
   const double* beta;
   const double* lnp2_fwd;       // (B) log2 P
   int32_t log2_alpha, log2_beta;  // linear sweeps: the utterance's array holds log2 scores
@@ -86,19 +87,46 @@ __device__ __forceinline__ double log_add2(double x, double y) {
 }
 
 // ---- weights and scores of the linear sweeps (rnnt_k2_linear.h)
-// A weight x (log2 units) as a probability, or as x itself (negative) below 2^-kLinearMinLog2;
-// an absent arc is 0.  Both carry lse2f in their low 16 bits like the log2 form; the bits make
-// 0 a subnormal below 2^-1056.
+// A weight x (log2 units) as a probability; below 2^-kLinearMinLog2 marked by its sign: the
+// negated probability down to 2^-kLinearMaxLog2, x itself past that, -0 for -inf.
+// An absent arc is 0.  Both weights of a row carry lse2f in their low 16 bits like the log2 form; the bits
+// make a 0 a subnormal below 2^-1056.
 constexpr double kLinearMinLog2 = 200.0;
+constexpr double kLinearMaxLog2 = 1000.0;
 __device__ __forceinline__ double code_weight(double x) {
-  return x >= -kLinearMinLog2 ? exp2(x) : (x < kNoArc ? kNoArc : x);  // NaN stays NaN
+  if (x < -kLinearMaxLog2) return x < kNoArc ? -0.0 : x;
+  const double p = exp2(x);  // NaN stays NaN
+  return x < -kLinearMinLog2 ? -p : p;
 }
 __device__ __forceinline__ double decode_weight(double w) {
-  return w < 0.0 ? w : w < 0x1p-1000 ? kNoArc : log2(w);
+  if (w <= -1.0) return w;
+  return fabs(w) < 0x1p-1010 ? kNoArc : log2(fabs(w));
 }
-// The exponent in the low 24 bits of a stored score m * 2^E, and the score's logarithm; a score
-// of 0 carries kZeroScore.
-constexpr int kZeroScore = -(1 << 23);
+// m * 2^e in a float64 and a separate integer exponent.
+struct Scaled {
+  double m;
+  int e;
+};
+constexpr int kZeroScore = -(1 << 23);              // the exponent a score of 0 is stored with
+constexpr int kNoScale = -(1 << 30) + kZeroScore;   // the exponent of 0 (its low 24 bits are kZeroScore's)
+constexpr int kNoWeight = -(1 << 29);               // ... of a weight of 0
+constexpr int kLowestExp = kZeroScore + 4096;       // ... of the smallest score but 0, past which it stays
+constexpr int kLowestWeight = -(1 << 26);           // ... of the smallest weight but 0
+// A weight of kernel 1's coded form.  The fraction of a log2 goes through the float32 exponential, whose
+// 1e-7 is what a step of the log2 sweeps rounds by.
+__device__ __forceinline__ Scaled scaled_weight(double w) {
+  Scaled o{fabs(w), 0};
+  if (w <= -1.0) {
+    const double f = floor(w);
+    o.m = static_cast<double>(fast_exp2(static_cast<float>(w - f)));
+    o.e = static_cast<int>(max(f, static_cast<double>(kLowestWeight)));
+  } else if (o.m < 0x1p-1010) {
+    o.m = 0.0;
+    o.e = kNoWeight;
+  }
+  return o;
+}
+// The exponent in the low 24 bits of a stored score m * 2^E, and the score's logarithm.
 __device__ __forceinline__ int score_exp(double x) { return (__double2loint(x) << 8) >> 8; }
 __device__ __forceinline__ double score_log2(double x) {
   const int e = score_exp(x);
@@ -127,11 +155,10 @@ __device__ __forceinline__ RowInfo lattice_row_record(const LatticeRecordSrc& s,
   const bool has_blank = t < T - 1 || closing, has_label = u < U;
   RowInfo o;
   o.lse2 = lse2;
-  if (CODED && !(s.log2_alpha | s.log2_beta) && lnP2 > 0.5 * kNoArc && !(w.x < 0.0) && !(w.y < 0.0)) {
+  if (CODED && !(s.log2_alpha | s.log2_beta) && lnP2 > 0.5 * kNoArc) {
     // scores m * 2^E, weights as probabilities: the product of the three mantissas, all in [0.5, 1),
-    // times a power of two from the exponents.  The sweeps bound a score only at the end of a chunk of
-    // diagonals; inside one its m may lie hundreds of binary orders below, where the product of the
-    // three numbers as they are would underflow (alpha 2^-482, weight 2^-23, beta 2^-593 of a posterior of 0.4)
+    // times a power of two from the exponents.  (A score's m goes down to 2^-801 and a weight to 2^-1000: the
+    // product of the numbers as they are would underflow.)
     const double eP = __builtin_rint(lnP2);
     const float fP = fast_exp2(static_cast<float>(eP - lnP2));  // 2^(eP) / P
     auto mant = [](double x) { return __builtin_amdgcn_frexp_mant(x); };
@@ -142,11 +169,15 @@ __device__ __forceinline__ RowInfo lattice_row_record(const LatticeRecordSrc& s,
       const float x = static_cast<float>(ldexp(m, e)) * fP;
       return x < 0x1p-126f ? 0.f : x;
     };
+    Scaled wb{w.x, 0}, wl{w.y, 0};
+    if (w.x < 0.0) wb = scaled_weight(w.x);
+    if (w.y < 0.0) wl = scaled_weight(w.y);
     const double dm = closing ? 1.0 : mant(b_down);
     const int e_down = closing ? 0 : expo(b_down) + score_exp(b_down);
-    o.occ_blank = has_blank ? posterior(am * mant(w.x) * dm, e0 + expo(w.x) + e_down) : 0.f;
+    o.occ_blank = has_blank ? posterior(am * mant(wb.m) * dm, e0 + expo(wb.m) + wb.e + e_down) : 0.f;
     o.occ_label =
-        has_label ? posterior(am * mant(w.y) * mant(b_right), e0 + expo(w.y) + expo(b_right) + score_exp(b_right)) : 0.f;
+        has_label ? posterior(am * mant(wl.m) * mant(b_right), e0 + expo(wl.m) + wl.e + expo(b_right) + score_exp(b_right))
+                  : 0.f;
   } else {
     double la = al, ld = b_down, lr = b_right, wx = w.x, wy = w.y;
     if (CODED) {

@@ -67,8 +67,8 @@ struct PopulateParams {
   int32_t n_ublk;          // blocks per frame
   int32_t rows_per_block;  // consecutive units u per block (<= kMaxRowsPerBlock)
   // lattice form
-  double2* lp2;            // (B, T_max, U_max+1) {lp_blank, lp_label} * log2(e)
-  int32_t linear;          // nonzero: the weights as probabilities (code_weight), absent arcs 0
+  double2* lp2;            // (B, T_max, U_max+1) {lp_blank, lp_label} * log2(e), or
+  int32_t linear;          // (nonzero) the weights as probabilities (code_weight), absent arcs 0
   int32_t pack_lse2f;      // nonzero: lse2f rides in the low bits of each row's two weights (the loss);
                            // zero: the weights as they are (forced alignment, whose ties stay exact)
   // dense form

@@ -68,10 +68,12 @@ struct LatticeParams {
   const int32_t* labels;  // (B, U_max) or null (lattice-only entry point)
   const int32_t* logit_lens;
   const int32_t* label_lens;
-  const double2* lp2;       // kernel 1's lattice form (log2 units, (B, T_max, U_max+1), kNoArc marks), or
+  const double2* lp2;       // kernel 1's lattice form (B, T_max, U_max+1): log2 units, kNoArc marks (scaled sweep: coded
+                            // probabilities), or
   const double* lp_blank;   // dense natural-log weights (B, T_max, U_max+1)
   const double* lp_label;
-  double* alpha;  // (B, T_max+U_max+1, u_pad), by diagonal, log2 units; rows past D_b + 1: spare
+  double* alpha;  // (B, T_max+U_max+1, u_pad), by diagonal, log2 units (scaled sweep: m and E, score_exp); rows past
+                  // D_b + 1: spare
   double* beta;
   int32_t u_pad;     // row width of alpha / beta: 64 * units per lane
   double* lnp2_fwd;  // (B) log2 P from the forward wave

@@ -1,50 +1,45 @@
-// Kernel 2 for lattices of up to 64 * kLinearWaves units: forward / backward scores as
-// scaled probabilities.
+// Kernel 2 for lattices of up to six columns of 64 units (scaled_sweep_columns): forward / backward
+// scores as scaled probabilities.
 //
 // The recursion of rnnt_k2_lattice.h with the scores as probabilities, not logarithms:
 //   alpha(t,u) = alpha(t-1,u) p_blank(t-1,u) + alpha(t,u-1) p_label(t,u-1)
-// so a step of a diagonal is two products, a lane shift and a fused multiply-add in
-// float64, where the log-add costs a conversion, an exponential, a logarithm and a
-// conversion back on the same dependent chain.  Every lane (one unit each) holds its score
-// as m * 2^E, with E an integer that stays fixed for a chunk of 8 diagonals and is set
-// anew, from m's exponent, between chunks; a neighbour's value enters times 2^(E' - E).
+// where the log-add has a conversion, an exponential, a logarithm and a conversion back on its
+// dependent chain.  Every lane (one unit each) holds its score as m * 2^e, e an integer of its own.
+// A step takes the larger of its two sources' exponents and scales the two weights by what the others
+// lie below it (off the chain of the scores): two products, a lane shift and a fused multiply-add, and
+// an exponent's shift and maximum beside them.  Every kNormEvery steps m goes back to [0.5, 1), its
+// exponent into e.
 //
-// What bounds a sweep is one wave's instruction issue (about 5 cycles an instruction) and that
-// chain, so the sweeping waves do little else: each has a loader wave, which reads the cells
+// Range.  There is none to be checked.  A lane whose exponent came from upstream along k <= kNormEvery arcs
+// since the last normalisation also holds that path's value, so its m is at least 2^-(200 k + 1), weights being
+// no less than 2^-kLinearMinLog2: a normal number, beside which what a term loses to underflow (2^-1074) is
+// below 2^-270.  Smaller weights are marked (rnnt_device.h).  Chunks that meet one decode their
+// weights, with exponents of their own where they are below 2^-1000, and normalise every step.
+// (An exponent fixed for a chunk of eight diagonals, as this kernel had first, makes a step two instructions
+// shorter, but each of its limits was met: by steep climbs on plain N(0, 3^2) logits, by alignments raised by
+// 20 to 40 nats, by any marked weight; the sweep was then done again, in all 3.5 times the time.
+// Checked and redone chunk by chunk, the decision at each chunk's end cost the chain 550 cycles.)
+//
+// What bounds a sweep is one wave's instruction issue (about 5 cycles an instruction, 14 to a step) and
+// its chains, so the sweeping waves do little else: each has a loader wave, which reads the cells
 // of 8 frames x 8 units as whole 128-byte lines into registers, several chunks ahead, and
 // writes them to LDS by diagonal; a step then reads one 16-byte row slot at a constant
 // offset, with no address arithmetic and no clamping (cells outside the utterance come back
-// as 0 from the bounded buffer, and 0 is the absent arc).  Kernel 2, this sweep against the
-// log2 one (event-timed): losses only, B=32 T=300 U=60, 25.2 -> 19.9 us; with scores, B=16
-// T=150 U=40 19.0 -> 15.4, B=32 T=250 U=80 36.5 -> 34.2 (W-Transducer 45.9 -> 36), B=64 T=500
-// U=150 86.7 -> 73, B=16 T=400 U=300 182 -> 115, B=8 T=400 U=383 223 -> 132 us.  A chunk is
-// ~640 cycles without scores to store, ~810 with, ~1400 with a neighbouring wave to exchange
-// with.  A wave touching the weights' lines ahead of the loaders changed nothing: not memory.
+// as 0 from the bounded buffer, and 0 is the absent arc).  A wave takes its neighbour's values two
+// chunks late, so that they too are in registers before their use.
 //
-// A chunk's scales are set from the scores four diagonals before it starts, in the shadow of
-// the steps in between, so that its start costs the chain one scaling.  A wave takes its
-// neighbour's values two chunks late, so that they too are in registers before their use.
-//
-// Exactness.  A probability below 2^-kLinearMinLog2 is stored by kernel 1 as its (negative)
-// log2 instead.  When a sweep met such a weight or a NaN, when a valid score at a chunk's end
-// lay outside [2^-kMinExp, 2^kMaxExp] of its lane's scale, or when some score up to 7 lanes
-// upstream lay more than kMaxRise binary orders above a lane, the block sweeps again with an
-// exponent of its own for every value (SLOW: no range limit, about ten times slower a step).
-// What a kept sweep loses to underflow in a chunk is below 2^-1022 in some lane's scale,
-// reaches another lane's scale multiplied by at most 2^kMaxRise, and valid scores there are
-// at least 2^-kMinExp: 2^-40 of any of them.  A score's fall (from the middle of a chunk to the end
-// of the next) is largest where the first chunks climb the labels of frame 0: under 170 on N(0, 3^2)
-// logits, 240 with an alignment's symbols raised by 8 nats, 250 by 12, 320 by 16 and 390 by 20 (N(0,
-// 2^2)); the rise over 7 lanes stays under 360 in all of them.  So one column has its limits at 410
-// and 572 (at 320 and 662, B=4 T=500 U=20 V=64 raised by 20 nats took 200 us a call, not 50).  Across
-// columns the rise is taken over up to 14 lanes, and the limits lie at 320 and 662 (at 410 and 572,
-// B=8 T=300 U=200 V=64 raised by 12 nats took 296 us, not 105).
+// Kernel 2, the log2 sweep / this one with an exponent a chunk / this one (event-timed, us): losses only, B=16
+// T=400 U=60 31 / 23.5 / 26.6, U=150 47 / 45 / 48, U=300 151 / 93 / 79; with scores, B=16 T=400 U=60 38 / 28 / 30
+// (W-Transducer 50 / 31 / 37), B=32 T=250 U=80 36.5 / 34.1 / 34.6 (46 / 37 / 40), B=64 T=500 U=150 73 / 82 / 81,
+// B=8 T=300 U=200 60 / 56 / 59, B=16 T=400 U=300 182 / 115 / 93, B=8 T=400 U=383 223 / 223 / 106.  The same with
+// symbols raised by 40 nats: 38 / 161 / 30 (U=60), 60 / 243 / 59 (U=200); T=400 U=300 on N(0, 3^2) 182 / 398 / 93.
+// Blanks masked in every frame, B=8 T=600 U=120: by -inf 67 / 331 / 85, by -1e4 67 / 387 / 98.
 //
 // Scores are stored by diagonal as before, 8 bytes a node: m with its low 24 mantissa bits
-// replaced by E (28 bits of m stay: 4e-9 relative, against the ~1e-7 of the float32
-// posteriors formed from them).  A sweep whose E would not fit (a path below 2^-8300000) is
-// run in log2 units by one wave (lattice_sweep); the two flags of an utterance tell
-// kernel 2b which of its arrays hold log2 scores.
+// replaced by e (28 bits of m stay: 4e-9 relative, against the ~1e-7 of the float32
+// posteriors formed from them).  An e below kLowestExp stays there, nothing beside a path probability
+// above 2^kLogScoresBelow; below that the sweep is run in log2 units by one wave (lattice_sweep).  The two
+// flags of an utterance tell kernel 2b which of its arrays hold log2 scores.
 #pragma once
 
 #include <type_traits>
@@ -57,16 +52,11 @@ namespace rnnt {
 constexpr int kChunk = 8;          // diagonals per chunk; also frames and units of a loaded tile
 constexpr int kTileRing = 24;      // LDS rows (diagonals) per column of 64 units
 constexpr int kTilesAhead = 4;     // chunks of weights in flight in a loader's registers
-constexpr int kScaleStep = 4;      // the next chunk's scales are set after this many steps
+constexpr int kNormEvery = 4;      // steps between two normalisations of a score
 constexpr int kWaveLag = 2;        // chunks between a wave and the neighbour it takes values from
-template <int NW>
-constexpr int kMinExp = NW == 1 ? 410 : 320;
-constexpr int kMaxExp = 450;  // with kMinExp and the weights' 2^-200: products of two scores and a weight are normal
-template <int NW>
-constexpr int kMaxRise = 1022 - 40 - kMinExp<NW>;  // lost terms stay below the kept ones
-constexpr int kMaxScale = (1 << 23) - 4096;  // |E| of a stored score
-constexpr int kNoScale = -(1 << 30);
-constexpr int kLowest = static_cast<int>(0x80000000u);
+constexpr int kLogScoresBelow = -(1 << 22);  // a path probability under 2^this has its scores in log2 units
+static_assert(kChunk % kNormEvery == 0 && kNormEvery * static_cast<int>(kLinearMinLog2) < 850,
+              "every wave normalises in the same steps, and m stays a normal number between two");
 static_assert(kTileRing >= 3 * kChunk - 1, "the next chunk being read and a tile being written");
 
 // LDS barrier: this wave's global loads and stores stay in flight.
@@ -76,27 +66,22 @@ __device__ __forceinline__ void k2_lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// The whole-wave shifts by one lane (0x138 up, 0x130 down); the end lane keeps `fill`, or 0.
-template <int CTRL, bool ZERO = false>
+// The whole-wave shifts by one lane (0x138 up, 0x130 down); the end lane keeps `fill`.
+template <int CTRL>
 __device__ __forceinline__ int wave_move(int x, int fill) {
-  return __builtin_amdgcn_update_dpp(ZERO ? 0 : fill, x, CTRL, 0xf, 0xf, ZERO);
+  return __builtin_amdgcn_update_dpp(fill, x, CTRL, 0xf, 0xf, false);
 }
-template <int CTRL, bool ZERO = false>
+template <int CTRL>
 __device__ __forceinline__ double wave_move(double x, double fill) {
-  const int lo = wave_move<CTRL, ZERO>(static_cast<int>(__double2loint(x)), static_cast<int>(__double2loint(fill)));
-  const int hi = wave_move<CTRL, ZERO>(static_cast<int>(__double2hiint(x)), static_cast<int>(__double2hiint(fill)));
+  const int lo = wave_move<CTRL>(static_cast<int>(__double2loint(x)), static_cast<int>(__double2loint(fill)));
+  const int hi = wave_move<CTRL>(static_cast<int>(__double2hiint(x)), static_cast<int>(__double2hiint(fill)));
   return __hiloint2double(hi, lo);
 }
 
-// m * 2^e in a float64 and a separate integer exponent, summed without overflow.
-struct Scaled {
-  double m;
-  int e;
-};
+// Sum without overflow; a zero's exponent does not count.
 __device__ __forceinline__ Scaled scaled_add(Scaled a, Scaled b) {
-  constexpr int kNone = -(1 << 30);
-  const int ea = a.m == 0.0 ? kNone : a.e + __builtin_amdgcn_frexp_exp(a.m);
-  const int eb = b.m == 0.0 ? kNone : b.e + __builtin_amdgcn_frexp_exp(b.m);
+  const int ea = a.m == 0.0 ? kNoScale : a.e + __builtin_amdgcn_frexp_exp(a.m);
+  const int eb = b.m == 0.0 ? kNoScale : b.e + __builtin_amdgcn_frexp_exp(b.m);
   const int e = max(ea, eb);
   const int da = min(max(a.e - e, -2100), 2100), db = min(max(b.e - e, -2100), 2100);
   return Scaled{ldexp(a.m, da) + ldexp(b.m, db), e};
@@ -107,33 +92,50 @@ __device__ __forceinline__ Scaled scaled_norm(Scaled a) {
   const int ex = __builtin_amdgcn_frexp_exp(a.m);
   return Scaled{ldexp(a.m, -ex), a.e + ex};
 }
-// A weight of kernel 1's coded form (rnnt_device.h).
-__device__ __forceinline__ Scaled scaled_weight(double w) {
-  const double f = floor(w);
-  if (w < 0.0) return Scaled{w <= 0.5 * kNoArc ? 0.0 : exp2(w - f), static_cast<int>(max(f, -1e9))};
-  return Scaled{w < 0x1p-1000 ? 0.0 : w, 0};
-}
 __device__ __forceinline__ Scaled scaled_mul(Scaled a, Scaled b) { return Scaled{a.m * b.m, a.e + b.e}; }
 
 typedef const volatile __attribute__((address_space(3))) u32x4* lds_volatile_u32x4;
+
+// A tile's weight as the loader leaves it: a log2 (-1 and below) as -m 2^0 with m = 2^fraction in [1, 2],
+// whose float32 leaves the low 29 bits free, and minus its exponent in them; any other as it is.
+__device__ __forceinline__ void split_log2(uint32_t& lo, uint32_t& hi) {
+  const double w = __hiloint2double(static_cast<int>(hi), static_cast<int>(lo));
+  const double f = floor(w);
+  const double m = max(static_cast<double>(fast_exp2(static_cast<float>(w - f))), 1.0);
+  const int e = static_cast<int>(max(f, static_cast<double>(kLowestWeight)));
+  const bool is_log2 = w <= -1.0;
+  lo = is_log2 ? static_cast<uint32_t>(-e) : lo;
+  hi = is_log2 ? static_cast<uint32_t>(__double2hiint(m)) | 0x80000000u : hi;
+}
+// ... as mantissa and exponent.  LOG2S: some weight of the tile is a log2.
+template <bool LOG2S>
+__device__ __forceinline__ Scaled tile_weight(double w) {
+  const bool is_log2 = LOG2S && w <= -1.0;
+  const int lo = __double2loint(w);
+  Scaled o{__hiloint2double(__double2hiint(w) & 0x7fffffff, is_log2 ? 0 : lo), is_log2 ? -lo : 0};
+  const bool none = o.m < 0x1p-1010;
+  o.m = none ? 0.0 : o.m;
+  o.e = none ? kNoWeight : o.e;
+  return o;
+}
 
 constexpr int kTileRow = kWave * 16;  // bytes of an LDS row: one column's cells of a diagonal
 template <int NW>
 struct LinearShared {
   alignas(16) unsigned char tile[NW][kTileRing * kTileRow];
-  // what a wave passes to its neighbour for chunk g, in slot g & 3 (slot w of the first index:
-  // between waves w and w + 1; the last one is of zeros, for the wave without a neighbour): the
-  // value of each step, the chunk's scale and the largest scale of the last 8 lanes; SLOW: a
-  // scale per step
+  alignas(8) int marked[NW][4][2];  // of chunk g's tiles, in slot g & 3: some weight is marked, some is a log2
+  // what a wave passes to its neighbour in the steps of chunk g, in slot g & 3 (slot w of the first
+  // index: between waves w and w + 1; the last one for the wave without a neighbour)
   alignas(16) double xch[NW][4][kChunk];
   alignas(16) int xexp[NW][4][kChunk];
-  alignas(8) int xhead[NW][4][2];
-  double sink[NW > 1 ? kWave + kChunk : 1];  // takes the steps' writes of the other lanes
+  // takes the steps' writes of the other lanes
+  double sink[NW > 1 ? kWave + kChunk : 1];
+  int sink_exp[NW > 1 ? kWave + kChunk : 1];
 };
 
 // One sweep by a block of NW sweeping waves of 64 units and NW loader waves behind them;
-// every thread returns whether its part has to be done in the next slower form.
-template <int NW, int VAR, int MODE, bool FWD, bool SLOW>
+// every thread returns whether the sweep has to be done in log2 units.
+template <int NW, int VAR, int MODE, bool FWD>
 __device__ __forceinline__ int linear_sweep(const LatticeParams& p, LinearShared<NW>& sh, int b, int T, int U) {
   constexpr int kRow = kTileRow;
   constexpr bool fwd = FWD;
@@ -176,15 +178,36 @@ __device__ __forceinline__ int linear_sweep(const LatticeParams& p, LinearShared
       __builtin_amdgcn_sched_barrier(0);
     };
     int ring = kTileRing - kChunk;  // first LDS row of the tile to write: tile -1 ends where chunk 0 starts
-    uint32_t sign = 0;  // sign bit: some weight is in log2 form
+    int n_put = 0;
+    uint32_t top_before = 0;
     auto put = [&](const u32x4 (&x)[8]) {
+      uint32_t top = 0;  // the largest upper word: marked weights have the sign bit, log2 ones are -1 and below
 #pragma unroll
-      for (int j = 0; j < 8; ++j) sign |= x[j].y | x[j].w;
+      for (int j = 0; j < 8; ++j) top = max(top, max(x[j].y, x[j].w));
+      const uint32_t both = max(top, top_before);  // tile g completes chunk g
+      const bool any_marked = __builtin_amdgcn_ballot_w64(both >= 0x80000000u) != 0;
+      const bool any_log2 = __builtin_amdgcn_ballot_w64(both >= 0xbff00000u) != 0;
+      if (lane == 0) {
+        sh.marked[wv][(n_put + 3) & 3][0] = any_marked;
+        sh.marked[wv][(n_put + 3) & 3][1] = any_log2;
+      }
+      top_before = top;
+      ++n_put;
       int row = ring + slot;
       row -= row >= kTileRing ? kTileRing : 0;
       unsigned char* dst = &sh.tile[wv][row * kRow + k * 16];
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(top >= 0xbff00000u) != 0, 0)) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) *reinterpret_cast<u32x4*>(dst + j * 128) = x[j];
+        for (int j = 0; j < 8; ++j) {
+          uint32_t y[4] = {x[j].x, x[j].y, x[j].z, x[j].w};
+          split_log2(y[0], y[1]);
+          split_log2(y[2], y[3]);
+          *reinterpret_cast<u32x4*>(dst + j * 128) = u32x4{y[0], y[1], y[2], y[3]};
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) *reinterpret_cast<u32x4*>(dst + j * 128) = x[j];
+      }
       ring += kChunk;
       ring -= ring >= kTileRing ? kTileRing : 0;
     };
@@ -216,7 +239,6 @@ __device__ __forceinline__ int linear_sweep(const LatticeParams& p, LinearShared
       }
       if (out) break;
     }
-    if (!SLOW && static_cast<int>(sign) < 0) bad = 1;
   } else {
     __builtin_amdgcn_s_setprio(3);
     const int ND = p.T_max + p.U_max;
@@ -224,32 +246,34 @@ __device__ __forceinline__ int linear_sweep(const LatticeParams& p, LinearShared
     const __amdgpu_buffer_rsrc_t s_rsrc = make_buffer(scores, static_cast<int64_t>(ND + 1) * p.u_pad * 8);
     const int row_bytes = p.u_pad * 8;
     const Scaled w_close = scaled_weight(w_utt[static_cast<int64_t>(T - 1) * U1 + U].x);
-    // a closing blank below the scales' range (its logit masked with a finite number, -1e30): the clamp of
-    // scaled_weight would be the loss, and the first score has no exponent to be stored with
-    if (w_close.m != 0.0 && w_close.e < -kMaxScale) bad = 1;
     const bool first_lane = fwd ? u == 0 : u == U;  // the node the sweep starts from
     const Scaled start = fwd ? Scaled{1.0, 0} : scaled_norm(w_close);
+    // the score of the diagonal reached, m * 2^e; a lane the sweep has not reached holds 0
     double m = first_lane ? start.m : 0.0;
-    int E = first_lane ? start.e : 0;
+    int e = first_lane && m != 0.0 ? max(start.e, kLowestExp) : kNoScale;
     Scaled acc{0.0, 0};  // W-Transducer: the sum of this lane's scores up to the chunk
-    auto store_score = [&](int d, double x, int ex) {
+    auto score_words = [&](double x, int ex) {  // the stored form
       const int lo = (__double2loint(x) & static_cast<int>(0xff000000)) | (ex & 0xffffff);
-      const u32x2 v = {static_cast<uint32_t>(lo), static_cast<uint32_t>(__double2hiint(x))};
-      __builtin_amdgcn_raw_buffer_store_b64(v, s_rsrc, u * 8, __builtin_amdgcn_readfirstlane(d * row_bytes), 0);
+      return u32x2{static_cast<uint32_t>(lo), static_cast<uint32_t>(__double2hiint(x))};
     };
-    // whether unit uu's node of diagonal d lies in the utterance
-    auto valid_at = [&](int d, int uu) { return uu >= d - (T - 1) && uu <= min(d, U) && uu >= 0; };
-    if (MODE != kLossOnly && first_lane) store_score(fwd ? 0 : D, m, m == 0.0 ? kZeroScore : E);
+    auto store_score = [&](int d, double x, int ex) {
+      __builtin_amdgcn_raw_buffer_store_b64(score_words(x, ex), s_rsrc, u * 8,
+                                            __builtin_amdgcn_readfirstlane(d * row_bytes), 0);
+    };
+    if (MODE != kLossOnly && first_lane) store_score(fwd ? 0 : D, m, e);
     const bool has_in = NW > 1 && (fwd ? wv > 0 : wv < NW - 1);    // a neighbour to take values from
     const bool has_out = NW > 1 && (fwd ? wv < NW - 1 : wv > 0);   // ... to pass them to
     const int in_slot = !has_in ? NW - 1 : fwd ? wv - 1 : wv;
     const int out_slot = fwd ? min(wv, NW > 1 ? NW - 2 : 0) : max(wv - 1, 0);
     const bool out_lane = has_out && lane == (fwd ? kWave - 1 : 0);
     constexpr int kToNext = fwd ? 0x138 : 0x130;  // the lane shift that brings the neighbour's value
+    // what enters where there is no neighbour: nothing, or a wild-card arc: of weight 1 from
+    // alpha(0,0) = 1 into (t, 0); from (t, U) to (T-1, U) (beta = w_close) or to the final state
+    const Scaled edge = fwd && VAR != 0 ? Scaled{1.0, 0} : Scaled{0.0, kNoScale};
+    const Scaled final_arc = VAR == 1 ? w_close : Scaled{1.0, 0};
     if (NW > 1 && wv == 0 && lane < 4 * kChunk) {
-      sh.xch[NW - 1][lane / kChunk][lane % kChunk] = 0.0;
-      sh.xexp[NW - 1][lane / kChunk][lane % kChunk] = 0;
-      sh.xhead[NW - 1][lane / kChunk][lane & 1] = (lane & 1) ? kNoScale : 0;
+      sh.xch[NW - 1][lane / kChunk][lane % kChunk] = edge.m;
+      sh.xexp[NW - 1][lane / kChunk][lane % kChunk] = edge.e;
     }
     int ring = 0;
     auto read_chunk = [&](double2 (&w)[kChunk]) {  // the weights of the next chunk
@@ -266,172 +290,129 @@ __device__ __forceinline__ int linear_sweep(const LatticeParams& p, LinearShared
       ring -= ring >= kTileRing ? kTileRing : 0;
     };
 
-    const Scaled wild = VAR == 0 ? Scaled{0.0, 0}
-                        : fwd    ? Scaled{u == 0 ? 1.0 : 0.0, 0}
-                                 : Scaled{u != U ? 0.0 : VAR == 1 ? w_close.m : 1.0, VAR == 1 ? w_close.e : 0};
-    // ^ the wild-card arcs that end where a lane has no neighbour: weight 1 from alpha(0,0) = 1 into
-    // (t, 0); from (t, U) to (T-1, U) (beta = w_close) or to the final state
-    int worst = 0;  // sign bit: a score or a scale out of range
-
-    // ---- SLOW: chunk g step by step, a = (m, E) an exponent to every value
-    auto slow_chunk = [&](int g, const double2 (&w)[kChunk]) {
-      const int d_cur = fwd ? g * kChunk : D - g * kChunk;  // the diagonal m is of
-      const int n_step = min(kChunk, D - g * kChunk);
-      Scaled a{m, E};
-#pragma unroll 1
-      for (int s = 0; s < n_step; ++s) {
-        double2 ws = w[0];
+    double x_in[kChunk];  // the neighbour's values for the chunk (NW > 1)
+    int e_in[kChunk];
+    auto read_in = [&](int g, double (&x)[kChunk], int (&ex)[kChunk]) {
 #pragma unroll
-        for (int k = 1; k < kChunk; ++k) {
-          ws.x = s == k ? w[k].x : ws.x;
-          ws.y = s == k ? w[k].y : ws.y;
-        }
-        if (VAR != 0) acc = scaled_add(acc, a);
-        const Scaled wl = scaled_weight(ws.y);
-        const Scaled out = fwd ? scaled_mul(a, wl) : a;
-        Scaled in{0.0, 0};
-        if (NW > 1) {
-          in.m = sh.xch[in_slot][g & 3][s];
-          in.e = sh.xexp[in_slot][g & 3][s];
-          if (out_lane) {
-            sh.xch[out_slot][g & 3][s] = out.m;
-            sh.xexp[out_slot][g & 3][s] = out.e;
-          }
-        }
-        in = Scaled{wave_move<kToNext>(out.m, in.m), wave_move<kToNext>(out.e, in.e)};
-        if (!fwd) in = scaled_mul(in, wl);
-        a = scaled_norm(scaled_add(scaled_mul(a, scaled_weight(ws.x)), in));
-        if (VAR != 0) a = scaled_norm(scaled_add(a, wild));
-        const int d = fwd ? d_cur + 1 + s : d_cur - 1 - s;
-        if (!valid_at(d, u)) a.m = 0.0;
-        if (a.m != 0.0 && (a.e > kMaxScale || a.e < -kMaxScale)) bad = 1;
-        if (MODE != kLossOnly) store_score(d, a.m, a.m == 0.0 ? kZeroScore : a.e);
+      for (int s = 0; s < kChunk; ++s) {
+        x[s] = sh.xch[in_slot][g & 3][s];
+        ex[s] = sh.xexp[in_slot][g & 3][s];
       }
-      m = a.m;
-      E = a.e;
     };
-
-    // ---- the scaled form
     // the rows of a whole chunk's steps as constant scalar offsets
     int row_off[kChunk];
 #pragma unroll
     for (int q = 0; q < kChunk; ++q) row_off[q] = __builtin_amdgcn_readfirstlane(q * row_bytes);
-    if (!SLOW) E = start.e;  // every lane: none but the first is reached
-    double ratio = 1.0;      // 2^(the neighbour's scale - this lane's), of the chunk
-    double x_in[kChunk];     // the neighbour's values for the chunk (NW > 1)
-    int rise_in = kNoScale;  // its largest scale near the edge
-    // a lane above U holds no node and its scale no meaning; less kNoScale the limit stays below 2^31
-    // (at 2^30 - 1 a scale above 1, as W-Transducer scores reach, wrapped and sent the sweep to SLOW)
-    const int rise_limit = u <= U ? kMaxRise<NW> : 1 << 29;
-    auto read_in = [&](int g, double (&x)[kChunk], int& e, int& rise) {
-#pragma unroll
-      for (int s = 0; s < kChunk; ++s) x[s] = sh.xch[in_slot][g & 3][s];
-      e = sh.xhead[in_slot][g & 3][0];
-      rise = sh.xhead[in_slot][g & 3][1];
-    };
-    // the scores of diagonal d: valid ones must be positive, normal (class 0x100) and in range.
-    // Sign bits: set in `out` where the lane has no node there, in `low` and `high` out of range
-    auto check_scores = [&](int d, double x) {
-      const int out = (u - (d - (T - 1))) | (min(d, U) - u);
-      int ex = __builtin_amdgcn_frexp_exp(x);
-      ex = __builtin_amdgcn_class(x, 0x100) ? ex : -100000;
-      worst |= ((ex + kMinExp<NW>) | (kMaxExp - ex)) & ~out;
-    };
-    auto fast_chunk = [&](int g, const double2 (&w)[kChunk], double2 (&w_next)[kChunk], auto whole_tag) {
-      constexpr bool whole = decltype(whole_tag)::value;
+
+    double in = edge.m;  // lane 0 resp. 63 keep theirs: the shifts write over it
+    int ei = edge.e;
+
+    // Chunk g, n_step diagonals of it.  WHOLE: all kChunk.  MARKED: some weights are (1) marked, (2) log2s; then
+    // all are decoded in the steps, with exponents of their own, and every step normalises its score.
+    auto steps = [&](int g, const double2 (&w)[kChunk], int n_step, auto whole_tag, auto marked_tag) {
+      constexpr bool WHOLE = decltype(whole_tag)::value;
+      constexpr int MARKED = decltype(marked_tag)::value;
       const int d_cur = fwd ? g * kChunk : D - g * kChunk;  // the diagonal m is of
-      const int n_step = whole ? kChunk : D - g * kChunk;
-      double x_next[kChunk];
-      int e_in = 0, rise_next = kNoScale;
-      if (NW > 1 && whole) read_in(g + 1, x_next, e_in, rise_next);
-      if (whole) read_chunk(w_next);
-      const int e_bits = E & 0xffffff;
-      const int chunk_off = u * 8 + (fwd ? d_cur + 1 : d_cur - kChunk) * row_bytes;
-      // no node of that lane is left (its arc would keep a lane alive that no other score follows)
-      const bool wild_over = fwd ? d_cur >= T - 1 : d_cur <= U;
-      const double c = VAR == 0 || wild_over ? 0.0 : ldexp(wild.m, min(max(wild.e - E, -2000), 1000));
-      double sum = 0.0;
+      const int store_off = u * 8 + (fwd ? d_cur + 1 : d_cur - kChunk) * row_bytes;
       double* const x_out = out_lane ? &sh.xch[out_slot][g & 3][0] : &sh.sink[NW > 1 ? lane : 0];
-      int E_next = E;
-      double ratio_next = 1.0;
+      int* const e_out = out_lane ? &sh.xexp[out_slot][g & 3][0] : &sh.sink_exp[NW > 1 ? lane : 0];
+      double sum = 0.0;  // of m, in e's scale
 #pragma unroll
-      for (int s = 0; s < (whole ? kChunk : kChunk - 1); ++s) {
-        if (!whole && s >= n_step) break;
-        const double wb = w[s].x, wl = w[s].y;
-        if (VAR != 0) sum += m;
-        const double t = VAR != 0 ? fma(m, wb, c) : m * wb;
-        const double out = fwd ? m * wl : m;
-        if (NW > 1) x_out[s] = out;
-        const double k = fwd ? ratio : wl * ratio;
-        if (NW > 1) x_in[s] = wave_move<kToNext>(out, x_in[s]);
-        m = fma(NW > 1 ? x_in[s] : wave_move<kToNext, true>(out, 0.0), k, t);
-        if (MODE != kLossOnly) {
-          if (whole) {
-            const int lo = (__double2loint(m) & static_cast<int>(0xff000000)) | e_bits;
-            const u32x2 x = {static_cast<uint32_t>(lo), static_cast<uint32_t>(__double2hiint(m))};
-            __builtin_amdgcn_raw_buffer_store_b64(x, s_rsrc, chunk_off, row_off[fwd ? s : kChunk - 1 - s], 0);
-          } else {
-            store_score(fwd ? d_cur + 1 + s : d_cur - 1 - s, m, E);
-          }
+      for (int s = 0; s < kChunk; ++s) {
+        if (!WHOLE && s >= n_step) break;
+        Scaled wb{w[s].x, 0}, wl{w[s].y, 0};
+        int n;
+        if (MARKED != 0) {
+          wb = tile_weight<MARKED == 2>(w[s].x);
+          wl = tile_weight<MARKED == 2>(w[s].y);
         }
-        if (whole && s == kScaleStep - 1) {
-          // the next chunk's scales; lanes the sweep has not reached take the last reached one's
-          const int d = fwd ? d_cur + kScaleStep : d_cur - kScaleStep;
-          const int front = (fwd ? min(d, U) : max(d - (T - 1), 0)) - ub;
-          E_next = E + __builtin_amdgcn_frexp_exp(m);
-          int e_front = __builtin_amdgcn_readlane(E_next, min(max(front, 0), kWave - 1));
-          if (NW > 1 && (fwd ? front < 0 : front >= kWave)) e_front = e_in;
-          E_next = (fwd ? lane > front : lane < front) ? e_front : E_next;
-          const int diff = wave_move<kToNext>(E_next, e_in) - E_next;
-          ratio_next = ldexp(1.0, min(max(diff, -1100), 1000));
+        if (VAR != 0) {
+          if (MARKED != 0) acc = scaled_add(acc, Scaled{m, e});
+          else sum += m;
         }
-        if (s == 0) {
-          // this chunk's scales: the largest of a node up to 7 lanes upstream (across the wave's
-          // edge: of the neighbour's last 8 lanes, for all of them) against each lane's
-          int rise = m != 0.0 ? E : kNoScale;
-#pragma unroll
-          for (int q = 0; q < kChunk - 1; ++q) rise = max(rise, wave_move<kToNext>(rise, kLowest));  // one v_max with the shift in it
-          if (out_lane) {
-            sh.xhead[out_slot][g & 3][0] = E;
-            sh.xhead[out_slot][g & 3][1] = rise;
-          }
-          if (NW > 1) rise = (fwd ? lane < kChunk - 1 : lane > kWave - kChunk) ? max(rise, rise_in) : rise;
-          worst |= rise_limit - (rise - E);
-          worst |= (kMaxScale - E) | (E + kMaxScale);
-        }
-      }
-      check_scores(fwd ? d_cur + n_step : d_cur - n_step, m);
-      if (VAR != 0) acc = scaled_add(acc, Scaled{sum, E});
-      if (whole) {
-        m = ldexp(m, E - E_next);
-        E = E_next;
-        ratio = ratio_next;
-        rise_in = rise_next;
+        const double out = fwd ? m * wl.m : m;
+        const int et = e + wb.e, eo = fwd ? e + wl.e : e;
         if (NW > 1) {
-#pragma unroll
-          for (int s = 0; s < kChunk; ++s) x_in[s] = x_next[s];
+          x_out[s] = out;
+          e_out[s] = eo;
+          in = x_in[s];
+          ei = e_in[s];
+        }
+        in = wave_move<kToNext>(out, in);
+        ei = wave_move<kToNext>(eo, ei);
+        // the scaling goes into the weights, off the chain of the scores (the exponents' own chain does not wait
+        // for them between normalisations)
+        if (fwd || VAR != 0) {
+          double r = fwd ? in : in * wl.m;
+          int er = fwd ? ei : ei + wl.e;
+          if (!fwd) {  // the label arc that unit U lacks
+            r = u == U ? final_arc.m : r;
+            er = u == U ? final_arc.e : er;
+          }
+          n = max(et, er);
+          m = fma(r, ldexp(1.0, er - n), m * ldexp(wb.m, et - n));
+        } else {
+          const int er = ei + wl.e;
+          n = max(et, er);
+          m = fma(in, ldexp(wl.m, er - n), m * ldexp(wb.m, et - n));
+        }
+        if (VAR != 0 && MARKED == 0) sum = ldexp(sum, et - n);
+        e = n;
+        if (MARKED != 0 || s % kNormEvery == kNormEvery - 1) {
+          const int ex = __builtin_amdgcn_frexp_exp(m);
+          const bool none = m == 0.0;
+          if (VAR != 0 && MARKED == 0) {
+            if (s == kChunk - 1) acc = scaled_add(acc, Scaled{sum, e});
+            else sum = ldexp(sum, -ex);  // of up to four scores, m above 2^-802: no overflow
+          }
+          m = __builtin_amdgcn_frexp_mant(m);
+          e = none ? kNoScale : max(e + ex, kLowestExp);
+        }
+        if (MODE != kLossOnly) {
+          if (WHOLE)
+            __builtin_amdgcn_raw_buffer_store_b64(score_words(m, e), s_rsrc, store_off, row_off[fwd ? s : kChunk - 1 - s],
+                                                  0);
+          else
+            store_score(fwd ? d_cur + 1 + s : d_cur - 1 - s, m, e);
         }
       }
     };
     double2 wa[kChunk], wb[kChunk];
+    int marked = 0, log2s = 0;  // of the chunk ahead's weights
+    using std::integral_constant;
     auto chunk = [&](int g, const double2 (&w)[kChunk], double2 (&w_next)[kChunk]) {
-      if (SLOW) {
+      if (D - g * kChunk >= kChunk) {
+        double x_next[kChunk];
+        int e_next[kChunk];
+        if (NW > 1) read_in(g + 1, x_next, e_next);
         read_chunk(w_next);
-        slow_chunk(g, w);
-      } else if (D - g * kChunk >= kChunk) {
-        fast_chunk(g, w, w_next, std::true_type{});
+        const int marked_next = sh.marked[wv][(g + 1) & 3][0], log2s_next = sh.marked[wv][(g + 1) & 3][1];
+        if (__builtin_expect(marked == 0, 1)) {
+          steps(g, w, kChunk, std::true_type{}, integral_constant<int, 0>{});
+        } else {
+          if (log2s == 0) steps(g, w, kChunk, std::true_type{}, integral_constant<int, 1>{});
+          else steps(g, w, kChunk, std::true_type{}, integral_constant<int, 2>{});
+        }
+        marked = __builtin_amdgcn_readfirstlane(marked_next);
+        log2s = __builtin_amdgcn_readfirstlane(log2s_next);
+        if (NW > 1) {
+#pragma unroll
+          for (int s = 0; s < kChunk; ++s) {
+            x_in[s] = x_next[s];
+            e_in[s] = e_next[s];
+          }
+        }
       } else {
-        fast_chunk(g, w, w_next, std::false_type{});
+        steps(g, w, D - g * kChunk, std::false_type{}, integral_constant<int, 2>{});  // the last one, whatever its weights
       }
     };
     k2_lds_barrier();  // tiles -1, 0 and 1 are in LDS
     read_chunk(wa);
+    marked = __builtin_amdgcn_readfirstlane(sh.marked[wv][0][0]);
+    log2s = __builtin_amdgcn_readfirstlane(sh.marked[wv][0][1]);
     k2_lds_barrier();
     for (int r = 0; r < lag; ++r) k2_lds_barrier();  // every wave passes one a round
-    if (!SLOW && NW > 1) {
-      int e0;
-      read_in(0, x_in, e0, rise_in);
-    }
+    if (NW > 1) read_in(0, x_in, e_in);
     for (int g = 0; g < n_round - lag; g += 2) {
       if (g < n_chunk) chunk(g, wa, wb);
       k2_lds_barrier();
@@ -439,23 +420,26 @@ __device__ __forceinline__ int linear_sweep(const LatticeParams& p, LinearShared
       if (g + 1 < n_chunk) chunk(g + 1, wb, wa);
       k2_lds_barrier();
     }
-    if (!SLOW && worst < 0) bad = 1;
-    Scaled total{m, E};
+    Scaled total{m, e};
     if (VAR != 0 && (fwd ? VAR == 1 && u == U : u == 0)) {
       // (t,U) -> (T-1,U), t <= T-2, resp. (0,0) -> (t,0), t >= 1: no later node reads the sum
       total = scaled_norm(scaled_add(total, acc));
       if (MODE != kLossOnly) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // after the step's store of the node
-        store_score(fwd ? D : 0, total.m, total.m == 0.0 ? kZeroScore : total.e);
+        store_score(fwd ? D : 0, total.m, total.m == 0.0 ? kNoScale : total.e);
       }
     }
+    // below 2^kLogScoresBelow the scores' stored exponents would not do (nor the clamps of the weights'
+    // and scores' exponents far below that)
     if (fwd && u == U) {
       Scaled P = scaled_mul(total, w_close);
       if (VAR == 2) P = scaled_add(P, acc);  // (t,U) -> final
       const double lnP2 = P.m == 0.0 ? kNoArc : log2(P.m) + static_cast<double>(P.e);
       p.lnp2_fwd[b] = lnP2;
       if (p.loss_f32) p.loss_f32[b] = static_cast<float>(-lnP2 / kLog2eD);
+      bad = P.m != 0.0 && lnP2 < kLogScoresBelow;
     }
+    if (!fwd && u == 0) bad = total.m != 0.0 && total.e + __builtin_amdgcn_frexp_exp(total.m) < kLogScoresBelow;
     __builtin_amdgcn_s_setprio(0);
   }
   return bad;
@@ -487,14 +471,8 @@ __global__ __launch_bounds__(128 * NW) void k2_linear(LatticeParams p) {
     return;  // the whole block
   }
 
-  int bad = fwd ? linear_sweep<NW, VAR, MODE, true, false>(p, sh, b, T, U)
-                : linear_sweep<NW, VAR, MODE, false, false>(p, sh, b, T, U);
+  int bad = fwd ? linear_sweep<NW, VAR, MODE, true>(p, sh, b, T, U) : linear_sweep<NW, VAR, MODE, false>(p, sh, b, T, U);
   bad = __syncthreads_or(bad);
-  if (bad) {
-    bad = fwd ? linear_sweep<NW, VAR, MODE, true, true>(p, sh, b, T, U)
-              : linear_sweep<NW, VAR, MODE, false, true>(p, sh, b, T, U);
-    bad = __syncthreads_or(bad);
-  }
   // the utterance's flags: in place of its backward ln P, which only the dense form reports
   if (tid == 0) reinterpret_cast<int32_t*>(p.lnp2_bwd + b)[fwd ? 0 : 1] = bad;
   if (bad && tid < kWave) {

@@ -23,10 +23,10 @@ def announce(request):
 
 def logits_of(x, y):
     """Logits of three symbols (blank 0, label 1, the rest) with p(blank) = 2^-x, p(label) = 2^-y."""
-    pb, pl = 2.0 ** -np.asarray(x, float), 2.0 ** -np.asarray(y, float)
-    rest = 1.0 - pb - pl
-    return np.stack([np.log(pb), np.log(pl), np.where(rest > 0, np.log(np.where(rest > 0, rest, 1.0)), -200.0)],
-                    axis=-1).astype(np.float32)
+    x, y = np.asarray(x, float), np.asarray(y, float)
+    rest = 1.0 - 2.0 ** -x - 2.0 ** -y
+    return np.stack([-x * np.log(2.0), -y * np.log(2.0),
+                     np.where(rest > 0, np.log(np.where(rest > 0, rest, 1.0)), -200.0)], axis=-1).astype(np.float32)
 
 
 def check(torch, pkg, logits, tl, ul, variant="rnnt"):  # noqa: F811
@@ -68,6 +68,99 @@ def test_steep_random_lattices(torch, pkg, variant, seed):  # noqa: F811
     tl = rng.integers(max(1, T // 2), T, size=B, endpoint=True)
     ul = rng.integers(0, U, size=B, endpoint=True)
     check(torch, pkg, logits_of(x, y), tl, ul, variant)
+
+
+# the same over several columns of 64 units (and their exchange), with weights down to the log2 form
+# (below 2^-1000) and arcs of probability 0; utterances that end inside an earlier column
+@pytest.mark.parametrize("variant", ["rnnt", "wrnnt", "wrnnt_allow_ignore"])
+@pytest.mark.parametrize("T,U", [(30, 40), (40, 63), (30, 70), (90, 64), (41, 127), (14, 150), (50, 190), (9, 255),
+                                 (12, 300), (70, 383)])
+def test_steep_lattices_over_columns(torch, pkg, variant, T, U):  # noqa: F811
+    rng = np.random.default_rng(T * 1000 + U)
+    B = 5
+    x, y = np.empty((2, B, T, U + 1))
+    for b, steep in enumerate([[1, 1, 2, 3, 30], [1, 1, 20, 50, 100, 199], [1, 1, 1, 400, 900], [1, 1, 990, 1010, 2500],
+                               [1, 1, 1, 1, 60, np.inf]]):
+        x[b] = rng.choice(steep, size=(T, U + 1))
+        y[b] = rng.choice(steep, size=(T, U + 1))
+    x[4, :, -1], y[4, 0] = 1.0, 1.0  # a path is left
+    tl, ul = np.full(B, T), np.full(B, U)
+    tl[1:4] = rng.integers(max(1, T // 2), T, size=3, endpoint=True)
+    ul[1:4] = rng.integers(U // 2, U, size=3, endpoint=True)
+    with np.errstate(divide="ignore", invalid="ignore"):
+        check(torch, pkg, logits_of(x, y), tl, ul, variant)
+
+
+# an alignment's symbols raised by up to 60 nats: past what a chunk's scales hold
+@pytest.mark.parametrize("variant", ["rnnt", "wrnnt", "wrnnt_allow_ignore"])
+@pytest.mark.parametrize("T,U,peak", [(90, 20, 40.0), (70, 63, 60.0), (100, 80, 30.0), (60, 110, 40.0), (90, 150, 25.0),
+                                      (60, 260, 45.0)])
+def test_sharp_alignments(torch, pkg, variant, T, U, peak):  # noqa: F811
+    rng = np.random.default_rng(U)
+    logits = rng.normal(0.0, 2.0, size=(3, T, U + 1, 7)).astype(np.float32)
+    tl = np.array([T, T - 7, max(1, T // 2)], np.int32)
+    ul = np.array([U, U // 2, U - 1], np.int32)
+    labels = rng.integers(1, 7, size=(3, U)).astype(np.int32)
+    for b in range(3):
+        frame = np.append(np.sort(rng.integers(0, tl[b], size=ul[b])), 1 << 30)
+        sym = np.where(np.arange(T)[:, None] >= frame, np.append(labels[b, :ul[b]], 0), 0)
+        np.put_along_axis(logits[b, :, :ul[b] + 1], sym[..., None],
+                          np.take_along_axis(logits[b, :, :ul[b] + 1], sym[..., None], 2) + np.float32(peak), 2)
+    loss, grad, seen = run_case(torch, pkg, logits, tl, ul, labels, variant=variant)
+    loss_ref, grad_ref = R.rnnt_loss_grad(seen, labels, tl, ul, 0, variant)
+    # a loss is a sum of T + U weights, each off by its float32 normaliser's last bit (2e-6 of up to 64 nats)
+    assert np.all(np.abs(loss - loss_ref) <= 1e-5 * np.abs(loss_ref) + 4e-6 * (T + U))
+    assert np.abs(grad - grad_ref).max() <= 4e-5
+
+
+# a NaN logit anywhere in an utterance: its loss and gradient are NaN, the others' are not
+@pytest.mark.parametrize("variant", ["rnnt", "wrnnt", "wrnnt_allow_ignore"])
+@pytest.mark.parametrize("T,U", [(30, 20), (60, 100), (20, 300)])
+def test_nan_stays_in_its_utterance(torch, pkg, variant, T, U):  # noqa: F811
+    rng = np.random.default_rng(U)
+    logits = rng.normal(0.0, 2.0, size=(4, T, U + 1, 6)).astype(np.float32)
+    for b, (t, u) in enumerate([(0, 0), (T // 2, U // 2), (T - 1, U)]):
+        logits[b, t, u, 3] = np.nan
+    labels = rng.integers(1, 6, size=(4, U)).astype(np.int32)
+    tl, ul = np.full(4, T, np.int32), np.full(4, U, np.int32)
+    loss, grad, seen = run_case(torch, pkg, logits, tl, ul, labels, variant=variant)
+    assert np.all(np.isnan(loss[:3])) and np.all(np.isnan(grad[:3]))
+    loss_ref, grad_ref = R.rnnt_loss_grad(seen[3:], labels[3:], tl[3:], ul[3:], 0, variant)
+    tol_check(loss[3:], grad[3:], loss_ref, grad_ref, "f32", tl[3:], ul[3:])
+
+
+# path probabilities below 2^-4194304: scores in log2 units, one wave a sweep, in every lattice and over columns
+@pytest.mark.parametrize("variant", ["rnnt", "wrnnt", "wrnnt_allow_ignore"])
+@pytest.mark.parametrize("T,U", [(12, 20), (30, 63), (12, 70), (40, 150), (20, 383)])
+def test_scores_in_log2_units(torch, pkg, variant, T, U):  # noqa: F811
+    rng = np.random.default_rng(T + U)
+    logits = rng.normal(0.0, 1.0, size=(3, T, U + 1, 5)).astype(np.float32)
+    logits[1] *= 3e6
+    labels = rng.integers(1, 5, size=(3, U)).astype(np.int32)
+    tl, ul = np.array([T, T, T - 3], np.int32), np.array([U, U, U // 2], np.int32)
+    loss, grad, seen = run_case(torch, pkg, logits, tl, ul, labels, variant=variant)
+    loss_ref, grad_ref = R.rnnt_loss_grad(seen, labels, tl, ul, 0, variant)
+    assert np.all(np.abs(loss - loss_ref) <= 1e-5 * np.abs(loss_ref))
+    for b in (0, 2):
+        assert np.abs(grad[b] - grad_ref[b]).max() <= 1e-5
+    assert np.all(np.isfinite(grad[1]))
+
+
+# path probabilities below 2^-4194304: scores in log2 units, one wave a sweep, in every lattice and over columns
+@pytest.mark.parametrize("variant", ["rnnt", "wrnnt", "wrnnt_allow_ignore"])
+@pytest.mark.parametrize("T,U", [(12, 20), (30, 63), (12, 70), (40, 150), (20, 383)])
+def test_scores_in_log2_units(torch, pkg, variant, T, U):  # noqa: F811
+    rng = np.random.default_rng(T + U)
+    logits = rng.normal(0.0, 1.0, size=(3, T, U + 1, 5)).astype(np.float32)
+    logits[1] *= 3e6
+    labels = rng.integers(1, 5, size=(3, U)).astype(np.int32)
+    tl, ul = np.array([T, T, T - 3], np.int32), np.array([U, U, U // 2], np.int32)
+    loss, grad, seen = run_case(torch, pkg, logits, tl, ul, labels, variant=variant)
+    loss_ref, grad_ref = R.rnnt_loss_grad(seen, labels, tl, ul, 0, variant)
+    assert np.all(np.abs(loss - loss_ref) <= 1e-5 * np.abs(loss_ref))
+    for b in (0, 2):
+        assert np.abs(grad[b] - grad_ref[b]).max() <= 1e-5
+    assert np.all(np.isfinite(grad[1]))
 
 
 # the closing blank masked with a finite number, down to float32's lowest: the loss is that number where
