@@ -167,8 +167,11 @@ def _stream_handle(device):
 # Workspace of a call whose caller passes none.  Taken from torch's allocator it is ordered on
 # the current stream, like the call's kernels, and costs a lookup; the library's own
 # hipMallocAsync went back to the driver after every synchronisation (B=16 T=400 U=300 V=32,
-# the first pass on new inputs: 824 us so, 338 us now).  None where the library refuses the shape
-# anyway, before it allocates anything.
+# the first pass on new inputs: 824 us so, 338 us now).  None, for the library to take its own, where
+# it refuses the shape anyway, before it allocates anything; where torch has no memory left, so that the
+# call's arguments are still checked first and its errors stay RNNTError; and under a stream capture: a
+# capture that torch did not begin would hand a block of torch's pool, free again after this call, to every
+# replay, where hipMallocAsync is captured with the kernels.
 @functools.lru_cache(maxsize=256)
 def _workspace_size(kind, B, T_max, U_max, V):
     if U_max + 1 > 2048 or T_max * (U_max + 1) >= 1 << 27:
@@ -180,7 +183,12 @@ def _call_workspace(nbytes, device):
     if not 0 < nbytes < 1 << 42:
         return None
     torch = _torch()
-    return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    if torch.cuda.is_current_stream_capturing():
+        return None
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
 
 
 def shape_of(logits, grad_dtype=None):

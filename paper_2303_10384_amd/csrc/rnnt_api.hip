@@ -444,14 +444,16 @@ rnnt_status_t rnnt_step_forward(const void* logits, rnnt_shape_t shape, const in
   const rnnt_status_t st = check_loss_args(logits, shape, labels, logit_lens, label_lens, blank, variant, loss_out,
                                            nullptr);
   if (st != RNNT_OK) return st;
-  if (!rows_out || !workspace) return RNNT_ERR_NULL_PTR;
-  if (!aligned16(rows_out) || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return RNNT_ERR_ALIGNMENT;
+  if (!rows_out) return RNNT_ERR_NULL_PTR;
+  if (!aligned16(rows_out)) return RNNT_ERR_ALIGNMENT;
   const Layout L = make_layout(shape, true);
-  if (workspace_bytes < L.total - L.lp2) return RNNT_ERR_WORKSPACE;
+  OwnedWorkspace owned;
+  char* ws = nullptr;
+  const rnnt_status_t st_ws = take_workspace(workspace, workspace_bytes, L.total - L.lp2, stream, owned, &ws);
+  if (st_ws != RNNT_OK) return st_ws;
   // the row records live in rows_out: the workspace is the layout from lp2 on
-  return run_rows(logits, shape, labels, logit_lens, label_lens, blank, variant, loss_out,
-                  static_cast<char*>(workspace) - L.lp2, L, static_cast<RowInfo*>(rows_out), keep_logits(shape, true),
-                  stream, nullptr);
+  return run_rows(logits, shape, labels, logit_lens, label_lens, blank, variant, loss_out, ws - L.lp2, L,
+                  static_cast<RowInfo*>(rows_out), keep_logits(shape, true), stream, nullptr);
 }
 
 rnnt_status_t rnnt_step_gradient(const void* logits, rnnt_shape_t shape, int32_t blank, const void* rows,

@@ -1,6 +1,6 @@
 // The loss in two calls, for the package's autograd wrapper (not part of the public C-ABI):
 // the losses and the row records of the gradient first, the gradient when the upstream
-// gradient is known.  Arguments as in rnnt_loss (include/rnnt_mi355x.h); nothing allocates.
+// gradient is known.  Arguments as in rnnt_loss (include/rnnt_mi355x.h); a given workspace is all they use.
 #pragma once
 
 #include "rnnt_mi355x.h"
@@ -17,7 +17,8 @@ size_t rnnt_step_workspace_bytes(rnnt_shape_t shape);
 int32_t rnnt_scaled_sweep_columns(int32_t U_max);
 
 // Losses, and in rows_out the row records: 16 bytes for each of the B * T_max * (U_max+1)
-// logits rows, 16-byte aligned.  workspace: 256-byte aligned, free again after the call's work.
+// logits rows, 16-byte aligned.  workspace: 256-byte aligned, free again after the call's work, or NULL (the
+// library takes one as in rnnt_loss).
 rnnt_status_t rnnt_step_forward(const void* logits, rnnt_shape_t shape, const int32_t* labels,
                                 const int32_t* logit_lens, const int32_t* label_lens, int32_t blank,
                                 rnnt_variant_t variant, float* loss_out, void* rows_out, void* workspace,
