@@ -141,3 +141,22 @@ def test_sweep_scales_past_the_stored_exponent(torch, pkg):  # noqa: F811
     for b in (0, 2):
         assert np.abs(grad[b] - grad_ref[b]).max() <= 1e-5
     assert np.all(np.isfinite(grad[1]))
+
+
+# rows of more than 2^16 elements, flat (their sum relative to the largest element is past the inherited shift's
+# limit) and in turn with rows of one dominant element; the bound of test_populate_kernel
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_flat_rows_of_many_elements(torch, pkg, dtype):  # noqa: F811
+    B, T, U, V = 1, 2, 12, 140001
+    rng = np.random.default_rng(1)
+    logits = rng.normal(0.0, 0.05, size=(B, T, U + 1, V)).astype(np.float32)
+    logits[0, 0, 1::3, 77] = 25.0
+    logits[0, 1, 5] -= 60.0
+    dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    lg = dev(logits).to(W.torch_dtype(dtype))
+    lse = pkg.log_softmax_gather(lg, dev(np.ones((B, U), np.int32)), dev(np.array([T], np.int32)),
+                                 dev(np.array([U], np.int32)), 0)[0].cpu().numpy()
+    z = lg.double().cpu().numpy()
+    m = z.max(axis=-1, keepdims=True)
+    ref = (m + np.log(np.exp(z - m).sum(axis=-1, keepdims=True)))[..., 0]
+    np.testing.assert_allclose(lse, ref, rtol=0, atol=1e-6)
