@@ -165,16 +165,18 @@ __device__ __forceinline__ int linear_sweep(const LatticeParams& p, LinearShared
     const int row_b = U1 * 16;
     const int step_g = (fwd ? kChunk : -kChunk) * row_b;
     const int step_j = 128 - kChunk * row_b;  // 8 units on, 8 frames back
-    // byte offset of tile -1's cell for j = 0
-    int off = ((fwd ? -kChunk : D - 15 + kChunk) - ub + i) * row_b + (ub + k) * 16;
+    // byte offset of tile -1's cell for j = 0; unsigned, the longest utterances' frames past T lie above 2^31 too
+    uint32_t off = static_cast<uint32_t>(((fwd ? -kChunk : D - 15 + kChunk) - ub + i)) * static_cast<uint32_t>(row_b) +
+                   static_cast<uint32_t>((ub + k) * 16);
     const int k_max = U - ub - k;  // unit 8 j + k of the column exists while 8 j <= k_max
     const int slot = fwd ? i + k : 14 - i - k;  // row of the cell after the tile's first row
     u32x4 buf[kTilesAhead][8];
     auto issue = [&](u32x4 (&x)[8]) {
 #pragma unroll
       for (int j = 0; j < 8; ++j)
-        x[j] = buffer_load16<false>(rsrc, 8 * j <= k_max ? off + j * step_j : kOutOfRange);
-      off += step_g;
+        x[j] = buffer_load16<false>(
+            rsrc, 8 * j <= k_max ? static_cast<int>(off + static_cast<uint32_t>(j * step_j)) : kOutOfRange);
+      off += static_cast<uint32_t>(step_g);
       __builtin_amdgcn_sched_barrier(0);
     };
     int ring = kTileRing - kChunk;  // first LDS row of the tile to write: tile -1 ends where chunk 0 starts

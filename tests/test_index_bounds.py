@@ -39,14 +39,38 @@ SHAPES = [(w.B, w.T_max, w.U_max, w.V, w.dtype) for w in WORKLOADS.values()] + [
     (1, 2, 1023, 3, "bf16"), (1, 3, 1535, 4, "f32"), (1, 2, 2047, 3, "bf16"), (3, 7, 5, 4100, "f32"), (3, 7, 5, 8200, "bf16"), (3, 7, 5, 2600, "f16")]
 
 
+def _constant(path, name):
+    """The value of `constexpr int name = ...;` (whole numbers, shifts and products of them)."""
+    expr = re.search(r"constexpr int %s = ([0-9 <*]+);" % name, open(os.path.join(_CSRC, path)).read()).group(1)
+    return int(eval(expr, {"__builtins__": {}}))
+
+
+K1_BLOCK_BYTES = _constant("rnnt_launch_k1.h", "kBlockBytes")
+K1_FILL_BLOCKS = _constant("rnnt_launch_k1.h", "kFillBlocks")
+K1_BLOCK_ROUNDS = _constant("rnnt_launch_k1.h", "kBlockRounds")
+K1_PIECE_CHUNKS = _constant("rnnt_launch_k1.h", "kPieceChunks")
+K1_MAX_ROWS = _constant("rnnt_k1_populate.h", "kMaxRowsPerBlock")
+
+
 def k1_shape(V, epc):
+    """(lanes per row, interior chunks per lane, whether a row fits the registers of one)."""
     interior = V // epc
     best, best_slots = (64, 5, False), 1 << 30
     for g in (8, 16, 32, 64):
         for nb in range(1, 6):
-            if g * nb >= interior and g * nb <= best_slots:
+            if g * nb >= interior and (g * nb < best_slots or (g * nb == best_slots and nb > 1)):
                 best, best_slots = (g, nb, True), g * nb
     return best
+
+
+def k1_blocking(B, T, U, V, esz, G):
+    """(blocks a frame, rows a block at most)."""
+    cap = K1_MAX_ROWS if esz != 4 else min(max(K1_BLOCK_BYTES // (V * esz), 32), K1_MAX_ROWS)
+    U1 = U + 1
+    n_ublk = -(-U1 // cap)
+    while B * T * n_ublk < K1_FILL_BLOCKS and -(-U1 // n_ublk) > K1_BLOCK_ROUNDS * (256 // G):
+        n_ublk += 1
+    return n_ublk, -(-U1 // n_ublk)
 
 
 @pytest.mark.parametrize("run", sorted({1, K1_XCD_RUN, 16}))
@@ -56,10 +80,12 @@ def test_populate_kernel_addresses(B, T, U, V, dt, run):
     esz = {"f32": 4, "bf16": 2, "f16": 2}[dt]
     n_elem = B * T * (U + 1) * V
     G, NB, fast = k1_shape(V, epc)
-    cap = 32 if dt == "f32" else 256  # consecutive units of one frame per block, at most
-    n_ublk = -(-(U + 1) // cap)
-    rows_per_block = -(-(U + 1) // n_ublk)  # equal blocks up to one unit
-    assert rows_per_block <= cap and (n_ublk - 1) * rows_per_block < U + 1
+    pieces = not fast  # rows past the registers go in pieces of 64 * K1_PIECE_CHUNKS interior chunks
+    if pieces:
+        G, NB = 64, K1_PIECE_CHUNKS
+    n_ublk, rows_per_block = k1_blocking(B, T, U, V, esz, G)  # equal blocks up to one unit
+    assert 1 <= rows_per_block <= K1_MAX_ROWS and n_ublk * rows_per_block >= U + 1
+    # (a frame cut to few rounds may end in blocks past its units: they return at once)
     blocks = B * T * n_ublk
     grid = -(-(-(-blocks // run)) // 8) * 8 * run
     assert grid < 2**31
@@ -71,7 +97,8 @@ def test_populate_kernel_addresses(B, T, U, V, dt, run):
     lb = ((k // run) * 8 + i % 8) * run + k % run
     kept = np.sort(lb[lb < blocks])
     assert np.array_equal(kept, np.arange(blocks))
-    fast = fast and rows_per_block * V * esz + 64 < 0x7fffffff
+    # the launcher checks the span with blocks of 64-lane groups, the largest that long rows have
+    fast = k1_blocking(B, T, U, V, esz, 64)[1] * V * esz + 64 < 0x7fffffff
     # every row a block can reach with full lengths (t < T, u <= U)
     b, t, u = np.meshgrid(np.arange(B), np.arange(T), np.arange(U + 1), indexing="ij")
     b, t, u = b.ravel(), t.ravel(), u.ravel()
@@ -90,7 +117,12 @@ def test_populate_kernel_addresses(B, T, U, V, dt, run):
         last_partial = (mis + V) % epc != 0
         kf = first_partial.astype(np.int64)
         kl = nch - 1 - last_partial.astype(np.int64)
-        assert np.all(kl - kf + 1 <= G * NB)
+        if pieces:  # lane k0 + 64 q of piece pc: every interior chunk once, the others past the buffer
+            n_pc = -(-(V // epc) // (64 * NB))
+            assert np.all(kl - kf + 1 <= n_pc * 64 * NB) and np.all(kl - kf + 1 > (n_pc - 1) * 64 * NB - epc)
+            assert int(nch.max() + n_pc * 64 * NB) * 16 < 2**31  # k * 16 in 32 bits, from an offset past the buffer too
+        else:
+            assert np.all(kl - kf + 1 <= G * NB)
         assert np.all(np.maximum(kl, 0) < nch) and np.all(kf <= nch)
     # only rows reaching into the tensor's final partial chunk read element-wise
     assert np.all((e0 + V > (n_elem // epc) * epc)[~whole])
@@ -117,12 +149,16 @@ def test_populate_kernel_addresses(B, T, U, V, dt, run):
     assert row.max() < B * T * (U + 1) and row.min() >= 0
 
 
-@pytest.mark.parametrize("B,T,U,V,dt", SHAPES)
-def test_gradient_kernel_chunk_mapping(B, T, U, V, dt):
-    epc = EPC[dt]
+# (logits, gradient): a chunk is 16 bytes of the gradient, 128 threads a block where that is float32
+GRADS = [(*s, s[4]) for s in SHAPES] + [(*s, "f32") for s in SHAPES if s[4] != "f32"]
+
+
+@pytest.mark.parametrize("B,T,U,V,dt,gdt", GRADS)
+def test_gradient_kernel_chunk_mapping(B, T, U, V, dt, gdt):
+    epc = EPC[gdt]
     n_elem = B * T * (U + 1) * V
     n_rows = B * T * (U + 1)
-    tile = (128 if dt == "f32" else 256) * 2  # threads x chunks per thread
+    tile = (128 if gdt == "f32" else 256) * 2  # threads x chunks per thread
     chunks = -(-n_elem // epc)
     blocks = -(-chunks // tile)
     assert blocks < 2**31
@@ -140,6 +176,9 @@ def test_gradient_kernel_chunk_mapping(B, T, U, V, dt):
         live = e0 < n_elem
         off = v_tile + cl * epc
         assert np.all(off < 2**32)
+        # split_row: e / V as a product with the rounded 1 / V, at most one off
+        q = (e_tile.astype(np.float64) * (1.0 / V)).astype(np.int64)
+        assert np.all(np.abs(q - r_tile) <= 1)
         dr = off // V
         r = r_tile + dr
         v = off - dr * V
@@ -153,7 +192,7 @@ def test_gradient_kernel_chunk_mapping(B, T, U, V, dt):
 
 @pytest.mark.parametrize("B,T,U,V,dt", SHAPES)
 def test_lattice_kernel_addresses(B, T, U, V, dt):
-    """Sweep kernel: weights of any step e read at the cell clamped into the utterance,
+    """Log2 sweep (the loss past six columns of units, rnnt_lattice_scores, and a scaled sweep's fallback): weights of any step e read at the cell clamped into the utterance,
     diagonal ec = clamp(e, 0, D), unit clamp(u, ec - (T_b-1), min(ec, U_b)), a valid cell,
     stored at its row (b, ec - u, u);
     alpha stored in row min(d, D+1), beta in row d (or the spare row ND when d < 0), each row
@@ -265,15 +304,17 @@ def test_wildcard_sums_take_each_frame_once(T, U):
     assert sorted(bwd) == list(range(1, T))
 
 
-@pytest.mark.parametrize("B,T,U,V,dt", SHAPES)
-def test_gradient_kernel_fast_path_buffer(B, T, U, V, dt):
+@pytest.mark.parametrize("B,T,U,V,dt,gdt", GRADS)
+def test_gradient_kernel_fast_path_buffer(B, T, U, V, dt, gdt):
     """Blocks on the buffer-load path: no partial chunk inside, a per-block buffer of at
     most one tile (offsets fit 32 bits), every live chunk's offset inside it, dead chunks
     past its end; the row-record indices of dead chunks are clamped into the records."""
-    epc = EPC[dt]
+    epc = EPC[gdt]
+    chunk_bytes = epc * {"f32": 4, "bf16": 2, "f16": 2}[dt]  # of logits: 16, or 8 under a float32 gradient
+    assert chunk_bytes in (8, 16)
     n_elem = B * T * (U + 1) * V
     n_rows = B * T * (U + 1)
-    tile = (128 if dt == "f32" else 256) * 2  # threads x chunks per thread
+    tile = (128 if gdt == "f32" else 256) * 2  # threads x chunks per thread
     n_chunks = -(-n_elem // epc)
     n_full = n_elem // epc
     blocks = -(-n_chunks // tile)
@@ -284,11 +325,11 @@ def test_gradient_kernel_fast_path_buffer(B, T, U, V, dt):
             # at most the last block holds the partial chunk
             assert V < epc or blk == blocks - 1
             continue
-        tile_bytes = min(tile, n_full - tile0) * 16
-        assert 0 < tile_bytes <= tile * 16 < 2**31
+        tile_bytes = min(tile, n_full - tile0) * chunk_bytes
+        assert 0 < tile_bytes <= tile * chunk_bytes < 2**31
         cl = np.arange(tile)
         live = tile0 + cl < n_full
-        assert np.all((cl * 16 < tile_bytes) == live)
+        assert np.all((cl * chunk_bytes < tile_bytes) == live)
         e_tile = tile0 * epc
         r_tile, v_tile = e_tile // V, e_tile % V
         r = np.minimum(r_tile + (v_tile + cl * epc) // V, n_rows - 1)
@@ -432,3 +473,149 @@ def test_columns_of_the_scaled_sweep(U_max, columns):
     reach one to six columns of the scaled sweep whatever their frames."""
     import paper_2303_10384_amd as P
     assert P.load_library().rnnt_scaled_sweep_columns(U_max) == columns
+
+
+CHUNK = _constant("rnnt_k2_linear.h", "kChunk")
+RING = _constant("rnnt_k2_linear.h", "kTileRing")
+WAVE_LAG = _constant("rnnt_k2_linear.h", "kWaveLag")
+NOTHING = (-1, -1)  # a cell that was never written, or holds the 0 of an offset past the buffer
+
+
+class ScaledSweep:
+    """One sweep of the scaled form: which cells its loaders put where in LDS between which barriers, and
+    what its sweeping waves read.  A phase is the work between two barriers."""
+
+    def __init__(self, T_max, U_max, T, U, fwd):
+        self.NW = (U_max + 64) // 64
+        self.T, self.U, self.U1, self.D, self.fwd = T, U, U_max + 1, T - 1 + U, fwd
+        self.size = T * self.U1 * 16
+        self.n_chunk = -(-self.D // CHUNK)
+        self.n_round = self.n_chunk + WAVE_LAG * (self.NW - 1)
+
+    def lag(self, wv):
+        return WAVE_LAG * (wv if self.fwd else self.NW - 1 - wv)
+
+    def tile(self, wv, g):
+        """Cells of tile g: [(LDS row after the tile's first, unit in the column, (frame, unit) or NOTHING)]."""
+        lane = np.arange(64)
+        i, k = lane >> 3, lane & 7
+        ub, row_b = wv * 64, self.U1 * 16
+        off = ((-CHUNK if self.fwd else self.D - 15 + CHUNK) - ub + i) * row_b + (ub + k) * 16
+        off = off + (g + 1) * (CHUNK if self.fwd else -CHUNK) * row_b
+        slot = i + k if self.fwd else 14 - i - k
+        cells = []
+        for j in range(8):
+            o = off + j * (128 - CHUNK * row_b)
+            assert np.all((o > -2**31) & (o < 2**32))  # unsigned 32 bits: below 0 is at or above 2^31
+            exists = 8 * j <= self.U - ub - k
+            unsigned = np.where(exists, o, 0x80000000) & 0xffffffff  # as the buffer's bounds check sees it
+            inside = unsigned < self.size
+            frame = (self.D - 15 - CHUNK * g if not self.fwd else CHUNK * g) - ub - 8 * j + i
+            unit = ub + 8 * j + k
+            assert np.array_equal(inside, exists & (frame >= 0) & (frame < self.T))
+            assert np.all(unit[inside] <= self.U) and np.array_equal((o // row_b)[inside], frame[inside])
+            assert np.array_equal((o % row_b // 16)[inside], unit[inside])
+            for n in range(64):
+                cells.append((int(slot[n]), int(8 * j + k[n]), (int(frame[n]), int(unit[n])) if inside[n] else NOTHING))
+        return cells
+
+    def check_column(self, wv):
+        lag, ring = self.lag(wv), {}
+        marks = {}
+        n_left = self.n_round - lag
+        # loader: tiles -1, 0, 1 in phase 0, tile g + 2 in the round of chunk g
+        puts = [(0, -1), (0, 0), (0, 1)] + [(2 + lag + g, g + 2) for g in range(n_left)]
+        # sweeping wave: chunk 0 in phase 1, chunk g + 1 in the round of chunk g where that is whole
+        reads = [(1, 0)] + [(2 + lag + g, g + 1) for g in range(min(n_left, self.n_chunk)) if self.D - CHUNK * g >= CHUNK]
+        phases = {}
+        for ph, g in puts:
+            phases.setdefault(ph, ([], []))[0].append(g)
+        for ph, g in reads:
+            phases.setdefault(ph, ([], []))[1].append(g)
+        for ph in sorted(phases):
+            written = set()
+            new = {}
+            for g in phases[ph][0]:
+                first = RING - CHUNK + (g + 1) * CHUNK
+                for slot, col, cell in self.tile(wv, g):
+                    assert 0 <= slot <= 14 and 0 <= col < 64
+                    key = ((first + slot) % RING, col)
+                    assert key not in written or ph == 0
+                    written.add(key)
+                    new[key] = cell
+                marks[g & 3] = (ph, g)
+            for g in phases[ph][1]:
+                for s in range(CHUNK):
+                    row = (g * CHUNK + s) % RING
+                    d = g * CHUNK + s if self.fwd else self.D - 1 - g * CHUNK - s
+                    for col in range(64):
+                        u = wv * 64 + col
+                        t = d - u
+                        want = (t, u) if 0 <= t < self.T and u <= self.U else NOTHING
+                        assert (row, col) not in written, "a row is written while it is read"
+                        got = ring.get((row, col), NOTHING)
+                        if g * CHUNK + s < self.D or want == NOTHING:  # a step of the sweep, or nothing there
+                            assert got == want, (wv, g, s, u, got, want)
+                # its marks were left by tile g, in an earlier phase
+                assert marks[g & 3][1] == g and marks[g & 3][0] < ph
+            ring.update(new)
+        # barriers: two before the rounds, the rounds before the first chunk, one a round
+        assert 2 + lag + n_left == 2 + self.n_round
+
+    def check_exchange(self):
+        """A wave reads the slot of chunk g + 1 in the round of chunk g (and slot 0 before its first round): written by
+        its neighbour for that chunk, in an earlier phase, and not written again meanwhile."""
+        for wv in range(self.NW):
+            src = wv - 1 if self.fwd else wv + 1
+            if not 0 <= src < self.NW:
+                continue
+            lag, lag_src = self.lag(wv), self.lag(src)
+            writes = {2 + lag_src + g: g for g in range(min(self.n_round - lag_src, self.n_chunk))}
+            wanted = [(2 + lag, 0)] if self.n_chunk else []
+            wanted += [(2 + lag + g, g + 1) for g in range(min(self.n_round - lag, self.n_chunk))
+                       if self.D - CHUNK * g >= CHUNK and g + 1 < self.n_chunk]
+            for ph, g in wanted:
+                before = [(p, c) for p, c in writes.items() if c % 4 == g % 4 and p < ph]
+                assert before and max(before)[1] == g
+                assert writes.get(ph, g + 1) % 4 != g % 4
+
+    def check_stores(self, T_max, U_max):
+        """Every step stores a row of its utterance's scores, in the columns the waves own."""
+        u_pad = 64 * units_per_lane(U_max + 1)
+        assert 64 * self.NW <= u_pad and (T_max + U_max + 1) * u_pad * 8 < 2**31
+        for g in range(self.n_chunk):
+            d_cur = CHUNK * g if self.fwd else self.D - CHUNK * g
+            n = min(CHUNK, self.D - CHUNK * g)
+            for s in range(n):
+                d = d_cur + 1 + s if self.fwd else d_cur - 1 - s
+                assert 0 <= d <= self.D <= T_max + U_max
+                if n == CHUNK:  # a constant row offset from the chunk's first row
+                    assert d == (d_cur + 1 if self.fwd else d_cur - CHUNK) + (s if self.fwd else CHUNK - 1 - s)
+
+
+@pytest.mark.parametrize("T,U", [(1, 0), (1, 7), (2, 1), (9, 0), (8, 1), (17, 63), (16, 64), (30, 65), (25, 127), (40, 192),
+                                 (3, 256), (33, 320), (11, 383), (90, 9), (57, 70)])
+def test_scaled_sweep_tiles_and_exchange(T, U):
+    """Every step reads the weights of its own cell, 0 where it has none; no LDS row is overwritten before it is
+    read or while it is; the exchange and the marks likewise; all waves pass the same barriers; utterances of the
+    padded shape, of one frame, without units and ending inside an earlier column."""
+    for T_b, U_b in {(T, U), (1, U), (T, 0), (max(1, T // 2), U // 2), (max(1, T - 3), max(0, U - 1))}:
+        for fwd in (True, False):
+            m = ScaledSweep(T, U, T_b, U_b, fwd)
+            for wv in range(m.NW):
+                m.check_column(wv)
+            m.check_exchange()
+            m.check_stores(T, U)
+
+
+def test_scaled_sweep_of_the_longest_utterances():
+    """Byte offsets of the loaders stay in 32 bits, past the buffer where they should be, at the largest
+    shapes the library takes (T_max * (U_max + 1) * 16 and the scores' rows under 2^31 bytes)."""
+    for U_max in (0, 63, 64, 383):
+        u_pad = 64 * units_per_lane(U_max + 1)
+        T = min((2**31 - 1) // (16 * (U_max + 1)), (2**31 - 1) // (u_pad * 8) - U_max - 1)
+        for fwd in (True, False):
+            m = ScaledSweep(T, U_max, T, U_max, fwd)
+            for wv in {0, m.NW - 1}:
+                for g in (-1, 0, 1, m.n_chunk // 2, m.n_chunk - 1, m.n_round + 1, m.n_round + 3):
+                    m.tile(wv, g)
