@@ -544,7 +544,7 @@ def main():
             "workload": w.describe(),
             "B": w.B, "T_max": w.T_max, "U_max": w.U_max, "V": V, "variant": w.variant,
             "valid_rows": r_valid, "padded_rows": r_total, "gradient_rows": ab["gradient_rows"],
-            "lattice_scores": "f64", "softmax": "f32",
+            "lattice_scores": "f64 (stored: 28 bits of mantissa, 24-bit exponent)" if w.U_max < 384 else "f64", "softmax": "f32",
         },
         "hbm_gbs_step": round(step_bytes / (ms_per_step * 1e-3) / 1e9, 1),
         "hbm_frac_step": round(step_bytes / (ms_per_step * 1e-3) / 1e9 / PEAK_HBM_GBS, 4),

@@ -12,6 +12,9 @@
 // for t >= 1 and (t,U)->(T-1,U) for t <= T-2.  Allow-ignore (Section 4.3): the
 // latter end in the final state instead.
 //
+// (The loss takes lattices of up to 384 units through the scaled sweep of rnnt_k2_linear.h; the sweep here takes
+// wider ones, dense weights, and what a scaled sweep hands on.)
+//
 // Schedule: the nodes of an anti-diagonal d = t + u depend only on diagonal
 // d-1 (forward) or d+1 (backward).  One wavefront sweeps the diagonals, lane j
 // owning the K consecutive units u = K*j .. K*j+K-1, so a step exchanges one

@@ -24,12 +24,7 @@ hipError_t launch_k2_k(const LatticeParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Up to 256 units a sweep takes one unit per lane over as many wavefronts as it
-// needs (the score rows keep the same 64 * units_per_lane columns); wider
-// lattices take one wavefront with several units per lane.
-#ifndef RNNT_K2_MULTI_WAVE
-#define RNNT_K2_MULTI_WAVE 1
-#endif
+// the scaled sweep, one to six columns of 64 units
 template <int NW, int VAR, int MODE>
 hipError_t launch_linear_nw(const LatticeParams& p, hipStream_t stream) {
   const int sweeps = (MODE == kLossOnly) ? 1 : 2;
@@ -58,20 +53,36 @@ hipError_t launch_linear(int variant, const LatticeParams& p, hipStream_t stream
   }
 }
 
+// The log2 sweep: of the loss past the scaled sweep's columns (eight units per lane and more), and of
+// dense weights of any width.
+// Up to 256 units a sweep takes one unit per lane over as many wavefronts as it
+// needs (the score rows keep the same 64 * units_per_lane columns); wider
+// lattices take one wavefront with several units per lane.
+#ifndef RNNT_K2_MULTI_WAVE
+#define RNNT_K2_MULTI_WAVE 1
+#endif
 template <int VAR, int MODE, bool DENSE_IN>
 hipError_t launch_k2_v(const LatticeParams& p, hipStream_t stream) {
-  switch (units_per_lane(p.U_max + 1)) {
-    case 1: return launch_k2_k<1, VAR, MODE, DENSE_IN>(p, stream);
+  const int K = units_per_lane(p.U_max + 1);
+  if constexpr (DENSE_IN) {
+    switch (K) {
+      case 1: return launch_k2_k<1, VAR, MODE, true>(p, stream);
 #if RNNT_K2_MULTI_WAVE
-    case 2: return launch_k2_k<1, VAR, MODE, DENSE_IN, 2>(p, stream);
-    case 3: return launch_k2_k<1, VAR, MODE, DENSE_IN, 3>(p, stream);
-    case 4: return launch_k2_k<1, VAR, MODE, DENSE_IN, 4>(p, stream);
+      case 2: return launch_k2_k<1, VAR, MODE, true, 2>(p, stream);
+      case 3: return launch_k2_k<1, VAR, MODE, true, 3>(p, stream);
+      case 4: return launch_k2_k<1, VAR, MODE, true, 4>(p, stream);
 #else
-    case 2: return launch_k2_k<2, VAR, MODE, DENSE_IN>(p, stream);
-    case 3: return launch_k2_k<3, VAR, MODE, DENSE_IN>(p, stream);
-    case 4: return launch_k2_k<4, VAR, MODE, DENSE_IN>(p, stream);
+      case 2: return launch_k2_k<2, VAR, MODE, true>(p, stream);
+      case 3: return launch_k2_k<3, VAR, MODE, true>(p, stream);
+      case 4: return launch_k2_k<4, VAR, MODE, true>(p, stream);
 #endif
-    case 6: return launch_k2_k<6, VAR, MODE, DENSE_IN>(p, stream);
+      case 6: return launch_k2_k<6, VAR, MODE, true>(p, stream);
+      default: break;
+    }
+  } else {
+    static_assert(scaled_sweep_columns(6 * kWave - 1) != 0, "narrower lattices of the loss take the scaled sweep");
+  }
+  switch (K) {
     case 8: return launch_k2_k<8, VAR, MODE, DENSE_IN>(p, stream);
     case 12: return launch_k2_k<12, VAR, MODE, DENSE_IN>(p, stream);
     case 16: return launch_k2_k<16, VAR, MODE, DENSE_IN>(p, stream);

@@ -69,3 +69,15 @@ def test_create_graph_and_repeated_training_steps(torch, pkg):  # noqa: F811
     with torch.no_grad():
         loss = pkg.RNNTLoss(reduction="none")(xr, y, tl, ul)
     assert not loss.requires_grad and torch.equal(loss, pkg.rnnt_loss(x, y, tl, ul, need_grad=False)[0])
+
+
+def test_logits_changed_between_the_two_calls(torch, pkg):  # noqa: F811
+    """The gradient is formed in backward from the saved logits: changing them in place before it is an error, as
+    with any operation that saves its input, and not a wrong gradient."""
+    x, y, tl, ul = make(torch, 33, "f32")
+    leaf = x.clone().requires_grad_(True)
+    xr = leaf * 1.0
+    loss = pkg.RNNTLoss(reduction="sum")(xr, y, tl, ul)
+    xr.mul_(2.0)
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        loss.backward()

@@ -416,7 +416,7 @@ def test_seeded_random_sweep(torch, pkg, chunk):
 
 @pytest.mark.parametrize("dtype,V,blank", [("f32", 4100, 17), ("bf16", 8200, 8199), ("f16", 2600, 0)])
 def test_large_vocabulary(torch, pkg, dtype, V, blank):
-    # rows longer than the populate kernel's register path (64 lanes x 5 chunks) take its batched path
+    # rows longer than the populate kernel's registers hold (64 lanes x 5 chunks) are taken in pieces
     logits, tl, ul, labels = W.small_case(3, 7, 5, V, seed=V, sigma=3.0, blank=blank)
     loss, grad, seen = run_case(torch, pkg, logits, tl, ul, labels, blank=blank, dtype=dtype)
     loss_ref, grad_ref = R.rnnt_loss_grad(seen, labels, tl, ul, blank, "rnnt")
